@@ -156,9 +156,7 @@ constexpr bool col_prefetch() {
 // z-update pass; xl2: lines per x-pass block relative to 256 threads, in halves.
 struct Sched {
   int ec32, ec64, bytes, ef32, ef64, fb32, fb64, xl2;
-  int xw = 0;    // x pass, FP32: minimum waves per SIMD for the register allocator (0: PSDNS_X_WAVES)
-  int xreg = 1;  // x pass, FP32: stage twiddles held in registers (else read from LDS)
-  int xpf = 1;   // x pass, FP32: first scalar pair loaded before the velocity transforms
+  int xreg = 1;  // x pass, FP32: stage factors held in registers (else read from LDS)
 };
 // bytes 0: the default of the size, 128-byte rows up to N = 512 and 64-byte rows above,
 // where 1024-thread blocks of 128-byte rows would exceed the register budget.
@@ -168,10 +166,10 @@ constexpr Sched kSched[] = {
     {16, 16, PSDNS_COL_BYTES, 16, 16, PSDNS_COL_BYTES, PSDNS_COL_BYTES, 2},                      // radix 16
     {PSDNS_EC32, PSDNS_EC64, 64, PSDNS_EF32, PSDNS_EF64, 64, 64, 2},                             // narrow tiles
     {PSDNS_EC32, PSDNS_EC64, PSDNS_COL_BYTES, PSDNS_EF32, PSDNS_EF64, PSDNS_FB32, PSDNS_FB64, 1},  // small x blocks
-    // x pass at three waves per SIMD: twiddles from LDS, no early scalar loads
-    {PSDNS_EC32, PSDNS_EC64, 0, PSDNS_EF32, PSDNS_EF64, 0, 0, 2, 3, 0, 0},
-    // the same with the twiddles kept in registers
-    {PSDNS_EC32, PSDNS_EC64, 0, PSDNS_EF32, PSDNS_EF64, 0, 0, 2, 3, 1, 0},
+    // x-pass factors from LDS
+    {PSDNS_EC32, PSDNS_EC64, 0, PSDNS_EF32, PSDNS_EF64, 0, 0, 2, 0},
+    // as the default
+    {PSDNS_EC32, PSDNS_EC64, 0, PSDNS_EF32, PSDNS_EF64, 0, 0, 2},
     // radix 16 on 64-byte tiles: at N = 1024 a column is one wavefront of 16 elements per
     // lane in 512-thread blocks, whose 256-register budget holds the fused pass unspilled
     // (in FP32 there the cap of col_max_threads gives schedules 0, 3, 5 and 6 this shape too)
@@ -208,9 +206,42 @@ struct Cfg {
   static constexpr int LX0 = 256 / TX * D.xl2 / 2;
   static constexpr int LX = LX0 < 1 ? 1 : (LX0 > 64 ? 64 : LX0);
   static constexpr int X_THREADS = LX * TX;
-  static constexpr int X_WAVES = (D.xw > 0 && F32) ? D.xw : PSDNS_X_WAVES;  // FP64 lines need the registers
+  // minimum waves per SIMD of the x pass: three in FP32 (512^3: 1.25 ms against 1.75 at two,
+  // where the register allocator hoists loads it cannot use; 256^3: 0.13 against 0.20), two in
+  // FP64, whose lines need the registers
+  static constexpr int X_WAVES = F32 ? 3 : PSDNS_X_WAVES;
   static constexpr int LP = LinePad<N>::value;
 };
+
+// Schedules whose kernels of a pass coincide at a size share one instantiation, that of the
+// lowest index: the column passes depend on (EC, W), the z-update pass on the same of its
+// own, the x pass on its lines per block and, in FP32, its register options.
+template <int N, typename T, int V, int U = 0>
+constexpr int canon_col() {
+  if constexpr (U == V || (Cfg<N, T, U>::EC == Cfg<N, T, V>::EC && Cfg<N, T, U>::W == Cfg<N, T, V>::W))
+    return U;
+  else
+    return canon_col<N, T, V, U + 1>();
+}
+template <int N, typename T, int V, int U = 0>
+constexpr int canon_fused() {
+  using A = typename Cfg<N, T, U>::Fused;
+  using B = typename Cfg<N, T, V>::Fused;
+  if constexpr (U == V || (A::EC == B::EC && A::W == B::W))
+    return U;
+  else
+    return canon_fused<N, T, V, U + 1>();
+}
+template <int N, typename T, int V, int U = 0>
+constexpr int canon_x() {
+  using A = Cfg<N, T, U>;
+  using B = Cfg<N, T, V>;
+  constexpr bool same = A::LX == B::LX && (sizeof(T) == 8 || A::D.xreg == B::D.xreg);
+  if constexpr (U == V || same)
+    return U;
+  else
+    return canon_x<N, T, V, U + 1>();
+}
 
 // Block placement of a column pass over (kx tile, row, slot).  Blocks are handed to the 8
 // XCDs round-robin in launch order (block L to XCD L mod 8), and each XCD has its own L2.
@@ -392,37 +423,134 @@ k_z_inverse(const cpx<T>* __restrict__ st, cpx<T>* __restrict__ abuf, const cpx<
 }
 
 // ---------------------------------------------------------------------------
+// forcing amplitude A = P / (2 E_f), E_f = 1/2 sum_{0<|k|^2<=kf^2} |u_hat|^2 / N^6 (FP64), of
+// one slot's stage input, by one block of any size: 256 partial sums (red, 256 doubles of LDS)
+// and a tree, so that the order of summation does not depend on the block.
+// ---------------------------------------------------------------------------
+constexpr int kForceParts = 256;
+template <typename T>
+__device__ __forceinline__ void forcing_block(const cpx<T>* __restrict__ sin, const SlotDev& sp, DynDev& dyn,
+                                              const Geom& g, int slot, double* red) {
+  // every stage starts a fresh grid maximum (only stage 0's x pass contributes to it)
+  if (threadIdx.x == 0) dyn.umax = 0ull;
+  if (sp.forcing != PSDNS_FORCING_POWER) {
+    // the hold scheme acts after the last stage only (k_band_hold)
+    if (threadIdx.x == 0) dyn.A = 0.0;
+    return;
+  }
+  int kf = 0;
+  while ((double)(kf + 1) * (kf + 1) <= sp.kf2) ++kf;
+  if (kf > g.K) kf = g.K;
+  const int span = 2 * kf + 1;
+  const int ncand = (kf + 1) * span * span;
+  const cpx<T>* base = sin + (long long)slot * g.F * g.st_field;
+  for (int p = threadIdx.x; p < kForceParts; p += blockDim.x) {
+    double e = 0.0;
+    for (int i = p; i < ncand; i += kForceParts) {
+      const int kx = i % (kf + 1);
+      const int ky = (i / (kf + 1)) % span - kf;
+      const int kz = i / ((kf + 1) * span) - kf;
+      const double k2 = double(kx) * kx + double(ky) * ky + double(kz) * kz;
+      if (k2 == 0.0 || k2 > sp.kf2) continue;
+      const int kyc = ky >= 0 ? ky : ky + g.M;
+      const int kzc = kz >= 0 ? kz : kz + g.M;
+      const long long o = st_row(kzc, kyc, g.M, g.PX) + kx;
+      double s = 0.0;
+      for (int f = 0; f < 3; ++f) {
+        const cpx<T> v = base[o + f * g.st_field];
+        s += double(v.x) * double(v.x) + double(v.y) * double(v.y);
+      }
+      e += (kx == 0 ? 0.5 : 1.0) * s;
+    }
+    red[p] = e;
+  }
+  __syncthreads();
+  for (int o = kForceParts / 2; o > 0; o >>= 1) {
+    for (int p = threadIdx.x; p < o; p += blockDim.x) red[p] += red[p + o];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) {
+    const double n3 = double(g.N) * g.N * g.N;
+    const double ef = red[0] / (n3 * n3);
+    dyn.A = (sp.power > 0.0 && ef > 0.0) ? sp.power / (2.0 * ef) : 0.0;
+  }
+}
+
+// step size from the stage-0 maxima (Eq. (10)) and the step record of one slot (one thread)
+static __device__ __forceinline__ void step_dt(DynDev& d, const Geom& g, double dt_arg) {
+  const double m = __longlong_as_double((long long)d.umax);
+  const double dx = 6.283185307179586476925286766559 / g.N;
+  double dt = dt_arg;
+  int fl = d.flags;
+  if (!(m == m) || m > 1.79769313486231570e308) fl |= PSDNS_FLAG_NONFINITE;
+  if (dt_arg < 0.0) dt = (m > 0.0 && m == m) ? (-dt_arg) * dx / m : 0.0;
+  if (dt * m / dx > 1.0) fl |= PSDNS_FLAG_CFL;
+  d.dt = dt;
+  d.max_u = m;
+  d.t += dt;
+  d.steps += 1;
+  d.flags = fl;
+}
+
+// the same as launches of their own, for the general kernels
+template <typename T>
+__global__ void __launch_bounds__(256)
+k_forcing_amplitude(const cpx<T>* __restrict__ sin, const SlotDev* __restrict__ slots, DynDev* __restrict__ dyn,
+                    Geom g) {
+  __shared__ double red[kForceParts];
+  const int slot = blockIdx.x;
+  if (!slots[slot].active) return;
+  forcing_block(sin, slots[slot], dyn[slot], g, slot, red);
+}
+static __global__ void __launch_bounds__(64)
+k_step_dt(const SlotDev* __restrict__ slots, DynDev* __restrict__ dyn, Geom g, double dt_arg) {
+  const int slot = blockIdx.x;
+  if (slots[slot].active && threadIdx.x == 0) step_dt(dyn[slot], g, dt_arg);
+}
+
+// ---------------------------------------------------------------------------
 // y inverse: columns along ky at fixed (z, kx-tile).
 // B fields: 0 u1, 1 u2, 2 u3, 3 omega1 = dy u3 - dz u2, 4 dz u1, 5 dy u1,
 //           6+3s phi_s, 7+3s dy phi_s, 8+3s dz phi_s   (x still spectral)
 // The next field's loads are issued before the current field is transformed.
 // DL = 1: the cube |ky| <= K of the phase-shift sphere; with shift the inputs carry
 // exp(i pi ky / N).
+// With fsin (the stage input) the grid has one more row, the first: its first block of each
+// slot computes the forcing amplitude, which the z pass of the stage reads.  A small grid is
+// bound by its launches, and this one rides along (32^3 FP64: six launches fewer of 22 per step
+// with the step size in the y forward, 193 us a step to 157).
 // ---------------------------------------------------------------------------
 template <int N, typename T, int V, int DL = 0>
 __global__ void PSDNS_COL_BOUNDS(Cfg<N, T, V>::COL_THREADS)
 k_y_inverse(const cpx<T>* __restrict__ abuf, cpx<T>* __restrict__ bbuf, const cpx<T>* __restrict__ tw_g,
-            const SlotDev* __restrict__ slots, Geom g, int shift = 0) {
+            const SlotDev* __restrict__ slots, Geom g, const cpx<T>* __restrict__ fsin, DynDev* __restrict__ dyn,
+            int shift = 0) {
   using C = Cfg<N, T, V>;
   constexpr int W = C::W, E = C::EC, TT = C::TC;
   constexpr int K = kmax<N, DL>();
   constexpr int M = 2 * K + 1;
   constexpr uint32_t CS = sizeof(cpx<T>);
   using L = ColLds<N, T, W>;
-  __shared__ cpx<T> smem[L::kEntries];
+  constexpr int kRed = kForceParts * (int)sizeof(double) / (int)CS;  // entries of the forcing sums
+  __shared__ cpx<T> smem[L::kEntries > kRed ? L::kEntries : kRed];
   __shared__ cpx<T> stw[N];
   __shared__ cpx<T> sph[DL ? N : 1];
-  const ColBlock cb = col_block<C::Col::PAIR>((g.KX + W - 1) / W, N);
+  const int extra = fsin ? 1 : 0;
+  const ColBlock cb = col_block<C::Col::PAIR>((g.KX + W - 1) / W, N + extra);
   if (!cb.ok) return;
   const int slot = cb.slot;
   if (!slots[slot].active) return;
+  if (cb.row < extra) {
+    if (cb.tile == 0) forcing_block(fsin, slots[slot], dyn[slot], g, slot, reinterpret_cast<double*>(smem));
+    return;
+  }
   if constexpr (DL) stage_shift<N, false>(sph, tw_g);
   stage_twiddles<N>(stw, tw_g);
   const cpx<T>* tw = stw;
   const int c = threadIdx.x % W;
   const int j = threadIdx.x / W;
   const int kx = cb.tile * W + c;
-  const int z = cb.row;
+  const int z = cb.row - extra;
   const bool valid = kx < g.KX;
   const typename L::View lds{smem + c};
   // A rows (z, ky_c) and B rows (z, y) are both PX entries apart at fixed z
@@ -758,7 +886,6 @@ k_x_pass(cpx<T>* __restrict__ bbuf, const cpx<T>* __restrict__ tw_g, const SlotD
   if constexpr (kLate) load(0, r0);
   build(r0, r1, h);
   const int S = g.S;
-  // first scalar pair's entries go in flight before the next transforms
   cpx<T> s0[NQ], s1[NQ], s2[NQ], s3[NQ], s4[NQ], s5[NQ];
   auto load_scalar_pair = [&](int s) {
     load(6 + 3 * s, s0);
@@ -770,8 +897,6 @@ k_x_pass(cpx<T>* __restrict__ bbuf, const cpx<T>* __restrict__ tw_g, const SlotD
       load(11 + 3 * s, s5);
     }
   };
-  constexpr bool kPrefetchScalars = sizeof(T) == 4 && !kLong && C::D.xpf;
-  if (kPrefetchScalars && S > 0) load_scalar_pair(0);
   fft<N, E, true, XS>(h, lds, j, tw);
   T u1p[E], u2p[E], c1[E], c2[E], c3[E];
   T mx = T(0);
@@ -842,7 +967,7 @@ k_x_pass(cpx<T>* __restrict__ bbuf, const cpx<T>* __restrict__ tw_g, const SlotD
       if constexpr (kLate) {
         load(6 + 3 * s, s0);
         load(7 + 3 * s, s1);
-      } else if (s > 0 || !kPrefetchScalars) {
+      } else {
         load_scalar_pair(s);
       }
       {
@@ -919,11 +1044,14 @@ k_x_pass(cpx<T>* __restrict__ bbuf, const cpx<T>* __restrict__ tw_g, const SlotD
 // ---------------------------------------------------------------------------
 // y forward: columns along y at fixed (z, kx-tile); keeps |ky| <= K.
 // The next field's loads are issued before the current field is transformed.
+// With dyn (stage 0 of a step) the grid has one more row, the first: its first block of each
+// slot sets the step size from the x pass's maximum and advances the step record.
 // ---------------------------------------------------------------------------
 template <int N, typename T, int V, int DL = 0>
 __global__ void PSDNS_YF_BOUNDS(Cfg<N, T, V>::COL_THREADS)
 k_y_forward(const cpx<T>* __restrict__ bbuf, cpx<T>* __restrict__ abuf, const cpx<T>* __restrict__ tw_g,
-            const SlotDev* __restrict__ slots, Geom g, int shift = 0, int afields = 0) {
+            const SlotDev* __restrict__ slots, Geom g, DynDev* __restrict__ dyn, double dt_arg, int shift = 0,
+            int afields = 0) {
   using C = Cfg<N, T, V>;
   constexpr int W = C::W, E = C::EC, TT = C::TC;
   constexpr int K = kmax<N, DL>();
@@ -933,17 +1061,22 @@ k_y_forward(const cpx<T>* __restrict__ bbuf, cpx<T>* __restrict__ abuf, const cp
   __shared__ cpx<T> smem[L::kEntries];
   __shared__ cpx<T> stw[N];
   __shared__ cpx<T> sph[DL ? N : 1];
-  const ColBlock cb = col_block<C::Col::PAIR>((g.KX + W - 1) / W, N);
+  const int extra = dyn ? 1 : 0;
+  const ColBlock cb = col_block<C::Col::PAIR>((g.KX + W - 1) / W, N + extra);
   if (!cb.ok) return;
   const int slot = cb.slot;
   if (!slots[slot].active) return;
+  if (cb.row < extra) {
+    if (cb.tile == 0 && threadIdx.x == 0) step_dt(dyn[slot], g, dt_arg);
+    return;
+  }
   if constexpr (DL) stage_shift<N, true>(sph, tw_g);
   stage_twiddles<N>(stw, tw_g);
   const cpx<T>* tw = stw;
   const int c = threadIdx.x % W;
   const int j = threadIdx.x / W;
   const int kx = cb.tile * W + c;
-  const int z = cb.row;
+  const int z = cb.row - extra;
   const bool valid = kx < g.KX;
   const typename L::View lds{smem + c};
   const uint32_t rsb = (uint32_t)g.PX * CS;
@@ -1529,60 +1662,6 @@ k_z_forward_pressure(const cpx<T>* __restrict__ abuf, cpx<T>* __restrict__ pout,
 }
 
 // ---------------------------------------------------------------------------
-// forcing amplitude A = P / (2 E_f), E_f = 1/2 sum_{0<|k|^2<=kf^2} |u_hat|^2 / N^6 (FP64)
-// ---------------------------------------------------------------------------
-template <typename T>
-__global__ void __launch_bounds__(256)
-k_forcing_amplitude(const cpx<T>* __restrict__ sin, const SlotDev* __restrict__ slots, DynDev* __restrict__ dyn,
-                    Geom g) {
-  __shared__ double red[256];
-  const int slot = blockIdx.x;
-  const SlotDev& sp = slots[slot];
-  if (!sp.active) return;
-  // every stage starts a fresh grid maximum (only stage 0's x pass contributes to it)
-  if (threadIdx.x == 0) dyn[slot].umax = 0ull;
-  if (sp.forcing != PSDNS_FORCING_POWER) {
-    // the hold scheme acts after the last stage only (k_band_hold)
-    if (threadIdx.x == 0) dyn[slot].A = 0.0;
-    return;
-  }
-  int kf = 0;
-  while ((double)(kf + 1) * (kf + 1) <= sp.kf2) ++kf;
-  if (kf > g.K) kf = g.K;
-  const int span = 2 * kf + 1;
-  const int ncand = (kf + 1) * span * span;
-  double e = 0.0;
-  const cpx<T>* base = sin + (long long)slot * g.F * g.st_field;
-  for (int i = threadIdx.x; i < ncand; i += 256) {
-    const int kx = i % (kf + 1);
-    const int ky = (i / (kf + 1)) % span - kf;
-    const int kz = i / ((kf + 1) * span) - kf;
-    const double k2 = double(kx) * kx + double(ky) * ky + double(kz) * kz;
-    if (k2 == 0.0 || k2 > sp.kf2) continue;
-    const int kyc = ky >= 0 ? ky : ky + g.M;
-    const int kzc = kz >= 0 ? kz : kz + g.M;
-    const long long o = st_row(kzc, kyc, g.M, g.PX) + kx;
-    double s = 0.0;
-    for (int f = 0; f < 3; ++f) {
-      const cpx<T> v = base[o + f * g.st_field];
-      s += double(v.x) * double(v.x) + double(v.y) * double(v.y);
-    }
-    e += (kx == 0 ? 0.5 : 1.0) * s;
-  }
-  red[threadIdx.x] = e;
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    const double n3 = double(g.N) * g.N * g.N;
-    const double ef = red[0] / (n3 * n3);
-    dyn[slot].A = (sp.power > 0.0 && ef > 0.0) ? sp.power / (2.0 * ef) : 0.0;
-  }
-}
-
-// ---------------------------------------------------------------------------
 // band-energy hold (the paper's deterministic forcing, Sec. 2.3), after the last stage:
 // E_f of y_{n+1} over 0 < |k|^2 <= kf^2 (FP64, the summation order of
 // k_forcing_amplitude), then the band modes of u scaled by sqrt(target / E_f)
@@ -1636,30 +1715,6 @@ k_band_hold(cpx<T>* __restrict__ state, const SlotDev* __restrict__ slots, Geom 
     long long o;
     if (!mode_at(i, o)) continue;
     for (int f = 0; f < 3; ++f) base[o + f * g.st_field] = fac * base[o + f * g.st_field];
-  }
-}
-
-// ---------------------------------------------------------------------------
-// step size from the stage-0 maxima (Eq. (10)) and the step record
-// ---------------------------------------------------------------------------
-static __global__ void __launch_bounds__(256)
-k_step_dt(const SlotDev* __restrict__ slots, DynDev* __restrict__ dyn, Geom g, double dt_arg) {
-  const int slot = blockIdx.x;
-  if (!slots[slot].active) return;
-  if (threadIdx.x == 0) {
-    DynDev& d = dyn[slot];
-    const double m = __longlong_as_double((long long)d.umax);
-    const double dx = 6.283185307179586476925286766559 / g.N;
-    double dt = dt_arg;
-    int fl = d.flags;
-    if (!(m == m) || m > 1.79769313486231570e308) fl |= PSDNS_FLAG_NONFINITE;
-    if (dt_arg < 0.0) dt = (m > 0.0 && m == m) ? (-dt_arg) * dx / m : 0.0;
-    if (dt * m / dx > 1.0) fl |= PSDNS_FLAG_CFL;
-    d.dt = dt;
-    d.max_u = m;
-    d.t += dt;
-    d.steps += 1;
-    d.flags = fl;
   }
 }
 
@@ -2093,7 +2148,7 @@ k_stats_z(const cpx<T>* __restrict__ st, cpx<T>* __restrict__ abuf, const cpx<T>
       const T kk = ax == 1 ? T(kx) : ax == 2 ? T(ky) : T(wave_of(j + TT * m, N));
       a[m] = ax == 0 ? v : mul_is(v, kk);
     }
-    fft<N, E, true>(a, lds, j, tw);
+    fft_dif<N, E, true>(a, lds, j, tw);
     if (valid) {
       cpx<T>* q = out + (long long)f * g.a_field;
 #pragma unroll
@@ -2130,7 +2185,7 @@ k_stats_y(const cpx<T>* __restrict__ abuf, cpx<T>* __restrict__ bbuf, const cpx<
       const int kc = compact_of(j + TT * m, N, K, M);
       a[m] = (valid && kc >= 0) ? p[kc * krow] : czero<T>();
     }
-    fft<N, E, true>(a, lds, j, tw);
+    fft_dif<N, E, true>(a, lds, j, tw);
     if (valid) {
       cpx<T>* q = out + (long long)f * g.b_field;
 #pragma unroll
@@ -2181,7 +2236,7 @@ k_x_moments(const cpx<T>* __restrict__ bbuf, const cpx<T>* __restrict__ tw_g, Ge
         for (int q = 0; q < NQ; ++q) rb[q] = czero<T>();
       }
       xl.build(ra, rb, h);
-      fft<N, E, true, typename XL::Sync>(h, lds, j, tw);
+      fft_dif<N, E, true, typename XL::Sync>(h, lds, j, tw);
 #pragma unroll
       for (int m = 0; m < E; ++m) {
         const double vx = h[m].x, vy = h[m].y;
@@ -2348,32 +2403,35 @@ struct TimedLaunch {
 template <int N, typename T, int V>
 struct Step {
   using C = Cfg<N, T, V>;
+  static constexpr int VC = canon_col<N, T, V>(), VX = canon_x<N, T, V>(), VF = canon_fused<N, T, V>();
   // x-pass blocks per slot, which is also the count of partial maxima k_step_dt reads
   static constexpr int kXBlocks = N * N / C::LX;
   static int ntile(const Geom& g) { return C::Col::grid_x((g.KX + C::W - 1) / C::W); }
 
   static void z_inverse(const Ctx& x, const cpx<T>* sin, hipStream_t s) {
     TimedLaunch tl(x.timer, KID_ZINV, s);
-    k_z_inverse<N, T, V><<<dim3(ntile(x.g), x.g.M, x.g.batch), C::COL_THREADS, 0, s>>>(
+    k_z_inverse<N, T, VC><<<dim3(ntile(x.g), x.g.M, x.g.batch), C::COL_THREADS, 0, s>>>(
         sin, static_cast<cpx<T>*>(x.abuf), static_cast<const cpx<T>*>(x.tw), x.slots, x.g);
   }
-  static void y_inverse(const Ctx& x, hipStream_t s) {
+  // with the forcing amplitude of the stage input sin
+  static void y_inverse(const Ctx& x, const cpx<T>* sin, hipStream_t s) {
     TimedLaunch tl(x.timer, KID_YINV, s);
-    k_y_inverse<N, T, V><<<dim3(ntile(x.g), N, x.g.batch), C::COL_THREADS, 0, s>>>(
+    k_y_inverse<N, T, VC><<<dim3(ntile(x.g), N + 1, x.g.batch), C::COL_THREADS, 0, s>>>(
         static_cast<const cpx<T>*>(x.abuf), static_cast<cpx<T>*>(x.bbuf), static_cast<const cpx<T>*>(x.tw), x.slots,
-        x.g);
+        x.g, sin, x.dyn);
   }
   // g carries nblk_x = kXBlocks
   static void x_pass(const Ctx& x, const Geom& g, int mode, hipStream_t s) {
     TimedLaunch tl(x.timer, KID_XPASS, s);
-    k_x_pass<N, T, V><<<dim3(kXBlocks, g.batch), C::X_THREADS, 0, s>>>(
+    k_x_pass<N, T, VX><<<dim3(kXBlocks, g.batch), C::X_THREADS, 0, s>>>(
         static_cast<cpx<T>*>(x.bbuf), static_cast<const cpx<T>*>(x.tw), x.slots, x.dyn, g, mode);
   }
-  static void y_forward(const Ctx& x, hipStream_t s) {
+  // set_dt (stage 0): also the step size and the step record
+  static void y_forward(const Ctx& x, bool set_dt, double dt_arg, hipStream_t s) {
     TimedLaunch tl(x.timer, KID_YFWD, s);
-    k_y_forward<N, T, V><<<dim3(ntile(x.g), N, x.g.batch), C::COL_THREADS, 0, s>>>(
+    k_y_forward<N, T, VC><<<dim3(ntile(x.g), N + (set_dt ? 1 : 0), x.g.batch), C::COL_THREADS, 0, s>>>(
         static_cast<const cpx<T>*>(x.bbuf), static_cast<cpx<T>*>(x.abuf), static_cast<const cpx<T>*>(x.tw), x.slots,
-        x.g);
+        x.g, set_dt ? x.dyn : nullptr, dt_arg);
   }
   // fuse: every stage of a multi-step call, the stage fixed at compile time
   static void z_forward(const Ctx& x, const StageArgs<T>& sa, int stage, bool fuse, hipStream_t s) {
@@ -2385,14 +2443,14 @@ struct Step {
     if (fuse) {
       TimedLaunch tl(x.timer, KID_ZFWDI, s);
       switch (stage) {
-        case 0: k_z_forward_update<N, T, true, V, 0><<<grid_u, TU, 0, s>>>(A, sa, tw, x.slots, x.dyn, g); break;
-        case 1: k_z_forward_update<N, T, true, V, 1><<<grid_u, TU, 0, s>>>(A, sa, tw, x.slots, x.dyn, g); break;
-        case 2: k_z_forward_update<N, T, true, V, 2><<<grid_u, TU, 0, s>>>(A, sa, tw, x.slots, x.dyn, g); break;
-        default: k_z_forward_update<N, T, true, V, 3><<<grid_u, TU, 0, s>>>(A, sa, tw, x.slots, x.dyn, g); break;
+        case 0: k_z_forward_update<N, T, true, VF, 0><<<grid_u, TU, 0, s>>>(A, sa, tw, x.slots, x.dyn, g); break;
+        case 1: k_z_forward_update<N, T, true, VF, 1><<<grid_u, TU, 0, s>>>(A, sa, tw, x.slots, x.dyn, g); break;
+        case 2: k_z_forward_update<N, T, true, VF, 2><<<grid_u, TU, 0, s>>>(A, sa, tw, x.slots, x.dyn, g); break;
+        default: k_z_forward_update<N, T, true, VF, 3><<<grid_u, TU, 0, s>>>(A, sa, tw, x.slots, x.dyn, g); break;
       }
     } else {
       TimedLaunch tl(x.timer, KID_ZFWD, s);
-      k_z_forward_update<N, T, false, V, -2><<<grid_u, TU, 0, s>>>(A, sa, tw, x.slots, x.dyn, g);
+      k_z_forward_update<N, T, false, VF, -2><<<grid_u, TU, 0, s>>>(A, sa, tw, x.slots, x.dyn, g);
     }
   }
 };
@@ -2428,23 +2486,19 @@ struct Stage {
     Geom g = x.g;
     with_sched<N>(x.psched[kPassX], [&](auto v) { g.nblk_x = Step<N, T, decltype(v)::value>::kXBlocks; });
     const cpx<T>* sin = static_cast<const cpx<T>*>(stage_in);
-    if (!(flags & kStagePrologue)) {
-      TimedLaunch tl(x.timer, KID_FORCE, s);
-      k_forcing_amplitude<T><<<g.batch, 256, 0, s>>>(sin, x.slots, x.dyn, g);
-    }
     if (flags & kStageZinv)
       with_sched<N>(x.psched[kPassZInverse], [&](auto v) { Step<N, T, decltype(v)::value>::z_inverse(x, sin, s); });
     if (flags & kStagePrologue) return;
-    with_sched<N>(x.psched[kPassYInverse], [&](auto v) { Step<N, T, decltype(v)::value>::y_inverse(x, s); });
+    with_sched<N>(x.psched[kPassYInverse], [&](auto v) { Step<N, T, decltype(v)::value>::y_inverse(x, sin, s); });
     with_sched<N>(x.psched[kPassX],
                   [&](auto v) { Step<N, T, decltype(v)::value>::x_pass(x, g, want_max ? kXMax : 0, s); });
-    if (stage == 0) {
-      TimedLaunch tl(x.timer, KID_DT, s);
-      k_step_dt<<<g.batch, 64, 0, s>>>(x.slots, x.dyn, g, dt_arg);
+    with_sched<N>(x.psched[kPassYForward],
+                  [&](auto v) { Step<N, T, decltype(v)::value>::y_forward(x, stage == 0, dt_arg, s); });
+    if (stage == 0 && x.stochastic) {
       // returns at once for slots without the stochastic forcing
+      TimedLaunch tl(x.timer, KID_DT, s);
       k_stochastic_update<T><<<g.batch, 256, 0, s>>>(static_cast<const cpx<T>*>(state), x.slots, x.dyn, x.fband, g);
     }
-    with_sched<N>(x.psched[kPassYForward], [&](auto v) { Step<N, T, decltype(v)::value>::y_forward(x, s); });
     StageArgs<T> sa;
     sa.yn = static_cast<cpx<T>*>(state);
     sa.acc = static_cast<cpx<T>*>(x.acc);
@@ -2475,10 +2529,6 @@ struct Stage {
     cpx<T>* A = static_cast<cpx<T>*>(x.abuf);
     cpx<T>* B = static_cast<cpx<T>*>(x.bbuf);
     cpx<T>* keep = static_cast<cpx<T>*>(x.akeep);
-    {
-      TimedLaunch tl(x.timer, KID_FORCE, s);
-      k_forcing_amplitude<T><<<g.batch, 256, 0, s>>>(sin, x.slots, x.dyn, g);
-    }
     if (flags & kStagePrologue) return;
     const int nt = St::ntile(g);
     for (int p = 0; p < 2; ++p) {
@@ -2488,7 +2538,8 @@ struct Stage {
       }
       {
         TimedLaunch tl(x.timer, KID_YINV, s);
-        k_y_inverse<N, T, 0, 1><<<dim3(nt, N, g.batch), C::COL_THREADS, 0, s>>>(A, B, tw, x.slots, g, p);
+        k_y_inverse<N, T, 0, 1><<<dim3(nt, N + 1 - p, g.batch), C::COL_THREADS, 0, s>>>(
+            A, B, tw, x.slots, g, p ? nullptr : sin, x.dyn, p);
       }
       {
         TimedLaunch tl(x.timer, KID_XPASS, s);
@@ -2496,15 +2547,15 @@ struct Stage {
         k_x_pass<N, T, kPhaseX, 1><<<dim3(Step<N, T, kPhaseX>::kXBlocks, g.batch), Cfg<N, T, kPhaseX>::X_THREADS, 0,
                                      s>>>(B, tw, x.slots, x.dyn, g, mode);
       }
-      if (stage == 0 && p == 0) {
-        TimedLaunch tl(x.timer, KID_DT, s);
-        k_step_dt<<<g.batch, 64, 0, s>>>(x.slots, x.dyn, g, dt_arg);
-        k_stochastic_update<T><<<g.batch, 256, 0, s>>>(static_cast<const cpx<T>*>(state), x.slots, x.dyn, x.fband, g);
-      }
+      const bool set_dt = stage == 0 && p == 0;
       {
         TimedLaunch tl(x.timer, KID_YFWD, s);
-        k_y_forward<N, T, 0, 1><<<dim3(nt, N, g.batch), C::COL_THREADS, 0, s>>>(B, p ? A : keep, tw, x.slots, g, p,
-                                                                                  p ? g.FA : g.F);
+        k_y_forward<N, T, 0, 1><<<dim3(nt, N + (set_dt ? 1 : 0), g.batch), C::COL_THREADS, 0, s>>>(
+            B, p ? A : keep, tw, x.slots, g, set_dt ? x.dyn : nullptr, dt_arg, p, p ? g.FA : g.F);
+      }
+      if (set_dt && x.stochastic) {
+        TimedLaunch tl(x.timer, KID_DT, s);
+        k_stochastic_update<T><<<g.batch, 256, 0, s>>>(static_cast<const cpx<T>*>(state), x.slots, x.dyn, x.fband, g);
       }
     }
     StageArgs<T> sa;
@@ -2596,11 +2647,11 @@ struct Engine {
     const int gx = C0::Col::grid_x(ntile);  // the passes shared with the step place blocks by col_block
     TimedLaunch tl(x.timer, KID_AUX, s);
     k_z_inverse<N, T, 0><<<dim3(gx, gp.M, gp.batch), C0::COL_THREADS, 0, s>>>(st, A, tw, x.slots, gp);
-    k_y_inverse<N, T, 0><<<dim3(gx, N, gp.batch), C0::COL_THREADS, 0, s>>>(A, B, tw, x.slots, gp);
+    k_y_inverse<N, T, 0><<<dim3(gx, N, gp.batch), C0::COL_THREADS, 0, s>>>(A, B, tw, x.slots, gp, nullptr, nullptr);
     k_x_pass<N, T, 0><<<dim3(gp.nblk_x, gp.batch), C0::X_THREADS, 0, s>>>(B, tw, x.slots, x.dyn, gp, kXPressure);
     Geom gy = gp;
     gy.F = 4;  // c1, c2, c3, |u|^2/2
-    k_y_forward<N, T, 0><<<dim3(gx, N, gp.batch), C0::COL_THREADS, 0, s>>>(B, A, tw, x.slots, gy);
+    k_y_forward<N, T, 0><<<dim3(gx, N, gp.batch), C0::COL_THREADS, 0, s>>>(B, A, tw, x.slots, gy, nullptr, 0.0);
     k_z_forward_pressure<N, T><<<dim3(ntile, gp.M, gp.batch), C0::COL_THREADS, 0, s>>>(A, P, tw, x.slots, gp);
     const long long per = (long long)N * N * (N / 2 + 1);
     k_fill_zero<T><<<(unsigned)((per * gp.batch + 255) / 256), 256, 0, s>>>(static_cast<cpx<T>*>(canon),

@@ -14,6 +14,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 namespace psdns {
 
 template <typename T>
@@ -89,8 +91,35 @@ __device__ __forceinline__ cpx<T> rot64(cpx<T> a, int m) {
   return {a.x * c - a.y * s, a.x * s + a.y * c};
 }
 
+__device__ __forceinline__ float fma_of(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_of(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
+// a + w b and a - w b with w = (c, s) a unit root, in six fused multiply-adds: four for the
+// sum t, then 2 a - t for the difference.  A product by the root followed by a sum and a
+// difference takes eight instructions and one rounding more in every component.
+template <bool INV, typename T>
+__device__ __forceinline__ void butterfly(cpx<T>& a, cpx<T>& b, cpx<T> w) {
+  if (INV) w.y = -w.y;
+  const cpx<T> t = {fma_of(-w.y, b.y, fma_of(w.x, b.x, a.x)), fma_of(w.y, b.x, fma_of(w.x, b.y, a.y))};
+  b = {fma_of(T(2), a.x, -t.x), fma_of(T(2), a.y, -t.y)};
+  a = t;
+}
+// a + w b and a - w b for the root w = exp(-+ 2 pi i m / 64), m known at compile time: the
+// trivial ones are sums and swaps, so inputs known to be zero fold away
+template <bool INV, typename T>
+__device__ __forceinline__ void butterfly64(cpx<T>& a, cpx<T>& b, int m) {
+  m &= 63;
+  if (m == 0 || m == 16) {
+    const cpx<T> r = rot64<INV>(b, m);
+    b = a - r;
+    a = a + r;
+  } else {
+    butterfly<INV>(a, b, cpx<T>{static_cast<T>(cos64(m)), static_cast<T>(-sin64(m))});
+  }
+}
+
 template <int R>
-__device__ constexpr int bitrev(int i) {
+__host__ __device__ constexpr int bitrev(int i) {
   int r = 0;
   for (int b = 1; b < R; b <<= 1) {
     r = (r << 1) | (i & 1);
@@ -99,10 +128,53 @@ __device__ constexpr int bitrev(int i) {
   return r;
 }
 
-// In-register R-point DFT (R a power of two, R <= 64): radix-2 decimation in
-// frequency followed by the bit-reversal permutation (free in registers).
+// In-register R-point DFT (R a power of two, R <= 64): bit-reversal permutation (free in
+// registers), then radix-2 decimation in time.  tw(len, k) gives the factor of butterfly k of
+// the sub-transforms of length len where the inputs carry stage twiddles: with inputs x_r w^r
+// the factor of level len is w^(R / len) exp(-2 pi i k / len), and k >= len / 4 is -i times
+// k - len / 4, so a stage needs R / 2 factors where separate twiddles need R - 1.  (FP32
+// 512-point lines: 196 vector instructions per lane and transform against 224.)
+struct NoTw {};
+// levels LEN, 2 LEN, .. of the transform, butterflies J, J + 1, .. of the level: the indices are
+// template arguments, so that every array stays in registers at any radix
+template <int R, bool INV, int LEN, int J, typename T, class Tw>
+__device__ __forceinline__ void dft_levels(cpx<T> (&b)[R], const Tw& tw) {
+  if constexpr (LEN <= R) {
+    constexpr int H = LEN / 2;
+    if constexpr (std::is_same_v<Tw, NoTw>) {
+#pragma unroll
+      for (int s = 0; s < R; s += LEN) butterfly64<INV>(b[s + J], b[s + J + H], J * (64 / LEN));
+    } else {
+      constexpr bool q = LEN >= 4 && 2 * J >= H;  // second quarter: -i (or +i) times the first
+      const cpx<T> w = tw.template get<LEN, (q ? J - H / 2 : J)>();
+#pragma unroll
+      for (int s = 0; s < R; s += LEN) {
+        cpx<T> v = b[s + J + H];
+        if constexpr (q) v = INV ? mul_i(v) : mul_mi(v);
+        butterfly<INV>(b[s + J], v, w);
+        b[s + J + H] = v;
+      }
+    }
+    if constexpr (J + 1 < H)
+      dft_levels<R, INV, LEN, J + 1>(b, tw);
+    else
+      dft_levels<R, INV, 2 * LEN, 0>(b, tw);
+  }
+}
+template <int R, bool INV, typename T, class Tw = NoTw>
+__device__ __forceinline__ void dft(cpx<T> (&a)[R], const Tw& tw = Tw{}) {
+  cpx<T> b[R];
+#pragma unroll
+  for (int i = 0; i < R; ++i) b[i] = a[bitrev<R>(i)];
+  dft_levels<R, INV, 2, 0>(b, tw);
+#pragma unroll
+  for (int i = 0; i < R; ++i) a[i] = b[i];
+}
+
+// The same DFT by radix-2 decimation in frequency and a bit-reversal permutation, for the
+// transforms whose input twiddles were applied apart (fft_dif and the general kernels).
 template <int R, bool INV, typename T>
-__device__ __forceinline__ void dft(cpx<T> (&a)[R]) {
+__device__ __forceinline__ void dft_dif(cpx<T> (&a)[R]) {
 #pragma unroll
   for (int len = R; len >= 2; len >>= 1) {
     const int half = len >> 1;
@@ -123,6 +195,9 @@ __device__ __forceinline__ void dft(cpx<T> (&a)[R]) {
 #pragma unroll
   for (int i = 0; i < R; ++i) a[i] = b[i];
 }
+
+// index among the R / 2 stage factors of factor (len, k), 0 <= k < max(1, len / 4)
+__host__ __device__ constexpr int tw_slot(int len, int k) { return len == 2 ? 0 : len / 4 + k; }
 
 // LDS views used for the inter-stage exchange; x is the running exchange index.
 // Columns: element p of the line owned by lane column c sits at base[p * W].  With
@@ -169,7 +244,7 @@ struct WaveSync {
   }
 };
 
-// Number of stage twiddles one thread applies (all stages after the first).
+// Number of stage factors one thread applies (all stages after the first; see dft).
 template <int N, int E, int NS = 1>
 __host__ __device__ constexpr int tw_count() {
   if constexpr (NS >= N) {
@@ -177,7 +252,7 @@ __host__ __device__ constexpr int tw_count() {
   } else {
     constexpr int R = (NS * E <= N) ? E : N / NS;
     constexpr int NB = E / R;
-    return (NS > 1 ? NB * (R - 1) : 0) + tw_count<N, E, NS * R>();
+    return (NS > 1 ? NB * (R / 2) : 0) + tw_count<N, E, NS * R>();
   }
 }
 
@@ -188,6 +263,13 @@ struct TwReg {
   static constexpr int C = tw_count<N, E>() > 0 ? tw_count<N, E>() : 1;
   cpx<T> w[C];
 };
+
+// table index of the stage factor (len, k): w^(R / len) exp(-2 pi i k / len) with
+// w = w_N^(kv N / (NS R)); below N for every kv < NS and k < max(1, len / 4)
+template <int N, int NS, int R>
+__device__ __forceinline__ int tw_index(int kv, int len, int k) {
+  return kv * (N / (NS * len)) + k * (N / len);
+}
 
 template <int N, int E, int NS, int OFF, typename T>
 __device__ __forceinline__ void tw_fill_stage(TwReg<N, E, T>& t, int j, const cpx<T>* __restrict__ tw) {
@@ -200,9 +282,12 @@ __device__ __forceinline__ void tw_fill_stage(TwReg<N, E, T>& t, int j, const cp
       for (int b = 0; b < NB; ++b) {
         const int kv = (j + TT * b) & (NS - 1);
 #pragma unroll
-        for (int r = 1; r < R; ++r) t.w[OFF + b * (R - 1) + r - 1] = tw[r * kv * (N / (NS * R))];
+        for (int len = 2; len <= R; len <<= 1)
+#pragma unroll
+          for (int k = 0; k < (len < 4 ? 1 : len / 4); ++k)
+            t.w[OFF + b * (R / 2) + tw_slot(len, k)] = tw[tw_index<N, NS, R>(kv, len, k)];
       }
-      tw_fill_stage<N, E, NS * R, OFF + NB * (R - 1)>(t, j, tw);
+      tw_fill_stage<N, E, NS * R, OFF + NB * (R / 2)>(t, j, tw);
     } else {
       tw_fill_stage<N, E, NS * R, OFF>(t, j, tw);
     }
@@ -216,14 +301,34 @@ __device__ __forceinline__ TwReg<N, E, T> tw_fill(int j, const cpx<T>* __restric
   return t;
 }
 
-// stage twiddle of butterfly b, element r: from a table (pointer) or from registers
+// stage factor (len, k) of butterfly b: from a table (pointer) or from registers
 template <int N, int E, int OFF, int R, typename T>
-__device__ __forceinline__ cpx<T> tw_get(const cpx<T>* __restrict__ tw, int b, int r, int idx) {
+__device__ __forceinline__ cpx<T> tw_get(const cpx<T>* __restrict__ tw, int b, int slot, int idx) {
   return tw[idx];
 }
 template <int N, int E, int OFF, int R, typename T>
-__device__ __forceinline__ cpx<T> tw_get(const TwReg<N, E, T>& t, int b, int r, int idx) {
-  return t.w[OFF + b * (R - 1) + r - 1];
+__device__ __forceinline__ cpx<T> tw_get(const TwReg<N, E, T>& t, int b, int slot, int idx) {
+  return t.w[OFF + b * (R / 2) + slot];
+}
+
+// the factors of one stage butterfly (see dft)
+template <int R, typename T>
+struct StageTw {
+  cpx<T> w[R / 2];
+  template <int LEN, int K>
+  __device__ __forceinline__ cpx<T> get() const {
+    return w[tw_slot(LEN, K)];
+  }
+};
+template <int N, int E, int NS, int OFF, int R, int LEN = 2, int K = 0, typename T, class Tw>
+__device__ __forceinline__ void stage_tw_fill(StageTw<R, T>& f, const Tw& tw, int b, int kv) {
+  if constexpr (LEN <= R) {
+    f.w[tw_slot(LEN, K)] = tw_get<N, E, OFF, R, T>(tw, b, tw_slot(LEN, K), tw_index<N, NS, R>(kv, LEN, K));
+    if constexpr (K + 1 < LEN / 4)
+      stage_tw_fill<N, E, NS, OFF, R, LEN, K + 1>(f, tw, b, kv);
+    else
+      stage_tw_fill<N, E, NS, OFF, R, 2 * LEN, 0>(f, tw, b, kv);
+  }
 }
 
 // Number of LDS exchanges of an N-point transform with E elements per thread.
@@ -255,14 +360,13 @@ __device__ __forceinline__ void fft_stage(cpx<T> (&v)[E], const Lds& lds, int j,
 #pragma unroll
       for (int r = 0; r < R; ++r) a[r] = v[b + r * NB];
       if constexpr (NS > 1) {
-#pragma unroll
-        for (int r = 1; r < R; ++r) {
-          cpx<T> w = tw_get<N, E, OFF, R, T>(tw, b, r, r * kv * (N / (NS * R)));
-          if (INV) w.y = -w.y;
-          a[r] = cmul(a[r], w);
-        }
+        // the R / 2 factors in one batch, before the arithmetic that needs them
+        StageTw<R, T> f;
+        stage_tw_fill<N, E, NS, OFF, R>(f, tw, b, kv);
+        dft<R, INV>(a, f);
+      } else {
+        dft<R, INV>(a);
       }
-      dft<R, INV>(a);
       if constexpr (LAST) {
 #pragma unroll
         for (int r = 0; r < R; ++r) v[b + r * NB] = a[r];
@@ -280,7 +384,7 @@ __device__ __forceinline__ void fft_stage(cpx<T> (&v)[E], const Lds& lds, int j,
       // would reuse this buffer first: after the last exchange of an odd count
       constexpr int NX = exchanges<N, E>();
       if constexpr (!Lds::kDouble || (XI + 1 == NX && NX % 2 == 1)) Sync::sync();
-      fft_stage<N, E, INV, NS * R, (NS > 1 ? OFF + NB * (R - 1) : OFF), Sync, XI + 1>(v, lds, j, tw);
+      fft_stage<N, E, INV, NS * R, (NS > 1 ? OFF + NB * (R / 2) : OFF), Sync, XI + 1>(v, lds, j, tw);
     }
   }
 }
@@ -292,6 +396,52 @@ __device__ __forceinline__ void fft_stage(cpx<T> (&v)[E], const Lds& lds, int j,
 template <int N, int E, bool INV, class Sync = BlockSync, typename T, class Lds, class Tw>
 __device__ __forceinline__ void fft(cpx<T> (&v)[E], const Lds& lds, int j, const Tw& tw) {
   fft_stage<N, E, INV, 1, 0, Sync>(v, lds, j, tw);
+}
+
+// The N-point transform of the statistics: the same stages and exchanges with separate input
+// twiddles and dft_dif.  An FP32 record holds single grid values (the velocity maximum) as FP64
+// numbers, so that its rounding shows in full; this keeps every record of a field the same
+// number from one release to the next.  The statistics are bound by memory either way.
+template <int N, int E, bool INV, class Sync = BlockSync, int NS = 1, typename T, class Lds>
+__device__ __forceinline__ void fft_dif(cpx<T> (&v)[E], const Lds& lds, int j, const cpx<T>* __restrict__ tw) {
+  if constexpr (NS < N) {
+    constexpr int TT = N / E;
+    constexpr int R = (NS * E <= N) ? E : N / NS;
+    constexpr int NB = E / R;
+    constexpr bool LAST = (NS * R == N);
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      const int vb = j + TT * b;
+      const int kv = vb & (NS - 1);
+      cpx<T> a[R];
+#pragma unroll
+      for (int r = 0; r < R; ++r) a[r] = v[b + r * NB];
+      if constexpr (NS > 1) {
+#pragma unroll
+        for (int r = 1; r < R; ++r) {
+          cpx<T> w = tw[r * kv * (N / (NS * R))];
+          if (INV) w.y = -w.y;
+          a[r] = cmul(a[r], w);
+        }
+      }
+      dft_dif<R, INV>(a);
+      if constexpr (LAST) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) v[b + r * NB] = a[r];
+      } else {
+        const int base = (vb / NS) * NS * R + kv;
+#pragma unroll
+        for (int r = 0; r < R; ++r) lds.st(base + r * NS, a[r], 0);
+      }
+    }
+    if constexpr (!LAST) {
+      Sync::sync();
+#pragma unroll
+      for (int m = 0; m < E; ++m) v[m] = lds.ld(j + TT * m, 0);
+      Sync::sync();
+      fft_dif<N, E, INV, Sync, NS * R>(v, lds, j, tw);
+    }
+  }
 }
 
 // Copy the N twiddles into LDS (block-wide; ends with a block barrier).

@@ -14,56 +14,6 @@ using gen::Factors;
 using gen::Shape;
 using gen::Spec;
 
-// Output fields of the z inverse: U1 U2 U3 dzU1 dzU2, then Phi_s dzPhi_s (axis 3 = kz).
-Spec z_inverse_spec(int S) {
-  Spec s{};
-  auto add = [&](int f, int axis) {
-    const int o = s.nout++;
-    s.nterm[o] = 1;
-    s.f[o][0] = f;
-    s.axis[o][0] = axis;
-    s.sgn[o][0] = 1.f;
-  };
-  add(0, 0);
-  add(1, 0);
-  add(2, 0);
-  add(0, 3);
-  add(1, 3);
-  for (int i = 0; i < S; ++i) {
-    add(3 + i, 0);
-    add(3 + i, 3);
-  }
-  return s;
-}
-
-// Output fields of the y inverse from the A fields (axis 2 = ky):
-// u1 u2 u3, omega1 = dy u3 - dz u2, dz u1, dy u1, then phi_s, dy phi_s, dz phi_s.
-Spec y_inverse_spec(int S) {
-  Spec s{};
-  auto add = [&](int f, int axis, float sg, int f2 = -1, int axis2 = 0, float sg2 = 0.f) {
-    const int o = s.nout++;
-    s.nterm[o] = f2 >= 0 ? 2 : 1;
-    s.f[o][0] = f;
-    s.axis[o][0] = axis;
-    s.sgn[o][0] = sg;
-    s.f[o][1] = f2 >= 0 ? f2 : 0;
-    s.axis[o][1] = axis2;
-    s.sgn[o][1] = sg2;
-  };
-  add(0, 0, 1.f);
-  add(1, 0, 1.f);
-  add(2, 0, 1.f);
-  add(2, 2, 1.f, 4, 0, -1.f);
-  add(3, 0, 1.f);
-  add(0, 2, 1.f);
-  for (int i = 0; i < S; ++i) {
-    add(5 + 2 * i, 0, 1.f);
-    add(5 + 2 * i, 2, 1.f);
-    add(6 + 2 * i, 0, 1.f);
-  }
-  return s;
-}
-
 // Plain inverse of the first nf A fields (statistics).
 Spec plain_spec(int nf) {
   Spec s{};
@@ -112,7 +62,7 @@ struct GEngine {
     const long long lines = (long long)g.N * g.N;
     gen::k_x_pass<T, P><<<dim3((unsigned)((lines + lw - 1) / lw), g.batch), 64 * lw, gen::x_lds_bytes(g.N, csize, lw),
                           s>>>(static_cast<cpx<T>*>(x.bbuf), static_cast<const cpx<T>*>(x.tw), x.slots, x.dyn, g,
-                               gen::factor(g.N), shift, umax);
+                               gen::step_factors(g.N), shift, umax);
   }
   // the line-moment kernel of the statistics: up to 256 threads per line
   static int moment_threads(const Geom& g) {
@@ -140,12 +90,34 @@ struct GEngine {
   static void x_pass(const Ctx& x, int shift, int umax, hipStream_t s) {
     with_positions(gen::x_positions(x.g.N), [&](auto p) { launch_x<decltype(p)::value>(x, shift, umax, s); });
   }
-  static void y_forward(const Ctx& x, void* out, int out_fields, int shift, hipStream_t s) {
+  // the column passes of the step
+  static Shape step_shape(const Factors& f) {
+    return gen::step_shape(f, (int)sizeof(cpx<T>), gen::col_threads<T>());
+  }
+  static void z_inverse_step(const Ctx& x, const void* in, int shift, hipStream_t s) {
     const Geom& g = x.g;
-    const Shape sh = shape(g);
-    gen::k_y_forward<T><<<dim3((g.KX + sh.W - 1) / sh.W, g.N, g.batch), sh.W * sh.TT, sh.lds, s>>>(
+    const Factors f = gen::step_factors(g.N);
+    const Shape sh = step_shape(f);
+    const T scale = T(1) / (T(g.N) * T(g.N) * T(g.N));
+    gen::k_z_inverse_step<T><<<dim3((g.KX + sh.W - 1) / sh.W, g.M, g.batch), sh.W * sh.TT, sh.lds, s>>>(
+        static_cast<const cpx<T>*>(in), static_cast<cpx<T>*>(x.abuf), static_cast<const cpx<T>*>(x.tw), x.slots, g, f,
+        sh.W, sh.TT, shift, scale);
+  }
+  static void y_inverse_step(const Ctx& x, int shift, hipStream_t s) {
+    const Geom& g = x.g;
+    const Factors f = gen::step_factors(g.N);
+    const Shape sh = step_shape(f);
+    gen::k_y_inverse_step<T><<<dim3((g.KX + sh.W - 1) / sh.W, g.N, g.batch), sh.W * sh.TT, sh.lds, s>>>(
+        static_cast<const cpx<T>*>(x.abuf), static_cast<cpx<T>*>(x.bbuf), static_cast<const cpx<T>*>(x.tw), x.slots,
+        g, f, sh.W, sh.TT, shift);
+  }
+  static void y_forward_step(const Ctx& x, void* out, int out_fields, int shift, hipStream_t s) {
+    const Geom& g = x.g;
+    const Factors f = gen::step_factors(g.N);
+    const Shape sh = step_shape(f);
+    gen::k_y_forward_step<T><<<dim3((g.KX + sh.W - 1) / sh.W, g.N, g.batch), sh.W * sh.TT, sh.lds, s>>>(
         static_cast<const cpx<T>*>(x.bbuf), static_cast<cpx<T>*>(out), out_fields, static_cast<const cpx<T>*>(x.tw),
-        x.slots, g, gen::factor(g.N), g.F, sh.W, sh.TT, shift);
+        x.slots, g, f, g.F, sh.W, sh.TT, shift);
   }
 
   // One evaluation of the right-hand side at stage_in and the update of `stage` (or dy/dt
@@ -160,17 +132,16 @@ struct GEngine {
       k_forcing_amplitude<T><<<g.batch, 256, 0, s>>>(sin, x.slots, x.dyn, g);
     }
     if (flags & kStagePrologue) return;
-    const Spec zs = z_inverse_spec(g.S), ys = y_inverse_spec(g.S);
     const int passes = g.sphere ? 2 : 1;
     for (int p = 0; p < passes; ++p) {
       const int shift = p;  // the second evaluation is on the shifted grid
       {
         TimedLaunch tl(x.timer, KID_ZINV, s);
-        z_inverse(x, stage_in, shift, zs, s);
+        z_inverse_step(x, stage_in, shift, s);
       }
       {
         TimedLaunch tl(x.timer, KID_YINV, s);
-        y_inverse(x, shift, ys, s);
+        y_inverse_step(x, shift, s);
       }
       {
         TimedLaunch tl(x.timer, KID_XPASS, s);
@@ -185,7 +156,7 @@ struct GEngine {
       {
         TimedLaunch tl(x.timer, KID_YFWD, s);
         const bool keep = g.sphere && p == 0;
-        y_forward(x, keep ? x.akeep : x.abuf, keep ? g.F : g.FA, shift, s);
+        y_forward_step(x, keep ? x.akeep : x.abuf, keep ? g.F : g.FA, shift, s);
       }
     }
     gen::GStage<T> sa;
@@ -207,7 +178,7 @@ struct GEngine {
     const Shape sh = gen::zf_shape(g.N, (int)sizeof(cpx<T>));
     gen::k_z_forward_update<T, P><<<dim3((g.KX + sh.W - 1) / sh.W, g.M, g.batch), sh.W * sh.TT, sh.lds, s>>>(
         static_cast<const cpx<T>*>(x.abuf), g.sphere ? static_cast<const cpx<T>*>(x.akeep) : nullptr, sa,
-        static_cast<const cpx<T>*>(x.tw), x.slots, x.dyn, g, gen::factor(g.N), sh.W, sh.TT);
+        static_cast<const cpx<T>*>(x.tw), x.slots, x.dyn, g, gen::step_factors(g.N), sh.W, sh.TT);
   }
 
   static void init_field(const Ctx& x, void* state, int slot, uint64_t seed, double kp, int kind, double energy,
@@ -311,7 +282,11 @@ struct GEngine {
                               hipFuncAttributeMaxDynamicSharedMemorySize, b);
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&gen::k_y_inverse<T>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, b);
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&gen::k_y_forward<T>),
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&gen::k_z_inverse_step<T>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, b);
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&gen::k_y_inverse_step<T>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, b);
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&gen::k_y_forward_step<T>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, b);
     for (int p = 1; p <= gen::kMaxPositions; ++p)
       with_positions(p, [&](auto q) {

@@ -122,7 +122,7 @@ __device__ __forceinline__ void stage(const cpx<T>* src, cpx<T>* dst, int W, int
     if constexpr (R % 2 == 1)
       dft_odd<R, INV>(a, root);
     else
-      dft<R, INV>(a);
+      dft_dif<R, INV>(a);
     const int base = bq * NS * R + kv;
 #pragma unroll
     for (int r = 0; r < R; ++r) dst[(base + r * NS) * W + c] = a[r];
@@ -152,6 +152,152 @@ __device__ __forceinline__ cpx<T>* fft(cpx<T>* b0, cpx<T>* b1, const Factors& f,
     }
     Sync::sync();
     NS *= R;
+    cpx<T>* t = src;
+    src = dst;
+    dst = t;
+  }
+  return src;
+}
+
+// ---------------------------------------------------------------------------
+// Transforms of the step kernels.  Their first stage takes its butterflies' inputs straight
+// from a functor (global memory) and their last one hands its outputs to one, so that a column
+// makes nst - 1 round trips through LDS with one barrier each, against nst + 1 with two more
+// barriers where every line is staged in and out (520^3 FP32: y inverse 2.61 ms).  Odd radices
+// come first: on a single line their stage writes R entries apart, free of bank conflicts for odd
+// R (radix 8 first: sixteen lanes on one bank), and the global loads of a wide first butterfly
+// are all in flight at once.  Power-of-two radices take the factors of fft.hpp's dft.
+// ---------------------------------------------------------------------------
+inline Factors step_factors(int N) {
+  Factors f{};
+  f.n = N;
+  int m = N;
+  for (int p : {13, 11, 7, 5, 3})
+    while (m % p == 0) {
+      f.r[f.nst++] = p;
+      m /= p;
+    }
+  // at least two stages
+  if (m == N && m == 8) {
+    f.r[f.nst++] = 4;
+    m = 2;
+  }
+  while (m % 8 == 0) {
+    f.r[f.nst++] = 8;
+    m /= 8;
+  }
+  if (m % 4 == 0) {
+    f.r[f.nst++] = 4;
+    m /= 4;
+  }
+  if (m % 2 == 0) f.r[f.nst++] = 2;
+  return f;
+}
+
+template <int R, typename T>
+struct TabTw {
+  const cpx<T>* tw;
+  int at, nr;  // kv N / (NS R) and N / R
+  template <int LEN, int K>
+  __device__ __forceinline__ cpx<T> get() const {
+    return tw[(at + K * nr) * (R / LEN)];
+  }
+};
+
+// butterfly of radix R with the stage factors w_N^(r at), at = kv N / (NS R) (0 in the first stage)
+template <int R, bool INV, bool FIRST, typename T>
+__device__ __forceinline__ void radix(cpx<T> (&a)[R], const cpx<T>* tw, int at, int N) {
+  if constexpr (R % 2 == 1) {
+    if constexpr (!FIRST) {
+#pragma unroll
+      for (int r = 1; r < R; ++r) {
+        cpx<T> w = tw[r * at];
+        if (INV) w.y = -w.y;
+        a[r] = cmul(a[r], w);
+      }
+    }
+    cpx<T> root[R];
+#pragma unroll
+    for (int m = 0; m < R; ++m) root[m] = tw[N + kRootOff(R) + m];
+    dft_odd<R, INV>(a, root);
+  } else if constexpr (FIRST) {
+    dft<R, INV>(a);
+  } else {
+    dft<R, INV>(a, TabTw<R, T>{tw, at, N / R});
+  }
+}
+
+// One stage: butterflies b = j, j + TT, .. < N/R with inputs src(b + r N/R), outputs to
+// dst(base + r NS, value).
+template <int R, bool INV, bool FIRST, typename T, class Src, class Dst>
+__device__ __forceinline__ void stage_io(const Src& src, const Dst& dst, int j, int TT, int N, int NS,
+                                         const cpx<T>* tw) {
+  const int nb = N / R;
+  const float rns = 1.0f / float(NS);  // exact quotients, as in stage()
+  const int step = FIRST ? 0 : nb / NS;
+  for (int b = j; b < nb; b += TT) {
+    const int bq = FIRST ? b : int((float(b) + 0.5f) * rns);
+    const int kv = FIRST ? 0 : b - bq * NS;
+    cpx<T> a[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) a[r] = src(b + r * nb);
+    radix<R, INV, FIRST>(a, tw, kv * step, N);
+    const int base = bq * NS * R + kv;
+#pragma unroll
+    for (int r = 0; r < R; ++r) dst(base + r * NS, a[r]);
+  }
+}
+template <bool INV, bool FIRST, typename T, class Src, class Dst>
+__device__ __forceinline__ void stage_of(int R, const Src& src, const Dst& dst, int j, int TT, int N, int NS,
+                                         const cpx<T>* tw) {
+  switch (R) {
+    case 2: stage_io<2, INV, FIRST>(src, dst, j, TT, N, NS, tw); break;
+    case 3: stage_io<3, INV, FIRST>(src, dst, j, TT, N, NS, tw); break;
+    case 4: stage_io<4, INV, FIRST>(src, dst, j, TT, N, NS, tw); break;
+    case 5: stage_io<5, INV, FIRST>(src, dst, j, TT, N, NS, tw); break;
+    case 7: stage_io<7, INV, FIRST>(src, dst, j, TT, N, NS, tw); break;
+    case 8: stage_io<8, INV, FIRST>(src, dst, j, TT, N, NS, tw); break;
+    case 11: stage_io<11, INV, FIRST>(src, dst, j, TT, N, NS, tw); break;
+    default: stage_io<13, INV, FIRST>(src, dst, j, TT, N, NS, tw); break;
+  }
+}
+
+// Transform of the W columns of a block from load(n) to store(n, value) through the line
+// buffers b0 and b1.  No barrier after the last stage: the buffers change places so that the
+// next transform's first stage writes the one that this last stage does not read.
+template <bool INV, typename T, class Load, class Store>
+__device__ __forceinline__ void fft_io(const Load& load, const Store& store, cpx<T>*& b0, cpx<T>*& b1,
+                                       const Factors& f, int W, int c, int j, int TT, const cpx<T>* tw) {
+  cpx<T>*src = b0, *dst = b1;
+  stage_of<INV, true, T>(f.r[0], load, [&](int n, cpx<T> v) { src[n * W + c] = v; }, j, TT, f.n, 1, tw);
+  __syncthreads();
+  int NS = f.r[0];
+  for (int st = 1; st + 1 < f.nst; ++st) {
+    stage_of<INV, false, T>(f.r[st], [&](int n) { return src[n * W + c]; },
+                            [&](int n, cpx<T> v) { dst[n * W + c] = v; }, j, TT, f.n, NS, tw);
+    __syncthreads();
+    NS *= f.r[st];
+    cpx<T>* t = src;
+    src = dst;
+    dst = t;
+  }
+  stage_of<INV, false, T>(f.r[f.nst - 1], [&](int n) { return src[n * W + c]; }, store, j, TT, f.n, NS, tw);
+  b0 = dst;
+  b1 = src;
+}
+// The same with the result left in LDS (returned; ends with a barrier, or a wave's own order).
+template <bool INV, class Sync = BlockSync, typename T, class Load>
+__device__ __forceinline__ const cpx<T>* fft_in(const Load& load, cpx<T>* b0, cpx<T>* b1, const Factors& f, int W,
+                                                int c, int j, int TT, const cpx<T>* tw) {
+  cpx<T>*src = b0, *dst = b1;
+  stage_of<INV, true, T>(f.r[0], load, [&](int n, cpx<T> v) { src[n * W + c] = v; }, j, TT, f.n, 1, tw);
+  Sync::sync();
+  int NS = f.r[0];
+  for (int st = 1; st < f.nst; ++st) {
+    stage_of<INV, false, T>(f.r[st], [&](int n) { return src[n * W + c]; },
+                            [&](int n, cpx<T> v) { dst[n * W + c] = v; }, j, TT, f.n, NS, tw);
+    Sync::sync();
+    NS *= f.r[st];
     cpx<T>* t = src;
     src = dst;
     dst = t;
@@ -197,6 +343,186 @@ inline Shape col_shape(int N, int csize) {
   if (s.TT > N / 2) s.TT = N / 2;
   s.lds = 2 * (size_t)s.W * N * csize;
   return s;
+}
+
+// Launch shape of the step's column passes: W columns, TT threads per column, the root table and
+// two line buffers in LDS.  A stage of radix R takes ceil((N/R) / TT) butterflies per thread, so
+// a TT that does not divide well leaves lanes idle in every stage (N = 520 with 64 threads per
+// column: 65 radix-8 butterflies in two turns).  TT is the multiple of a wavefront, between half
+// and all of the block's thread limit, that wastes least: the smallest TT times the sum over the
+// stages of turns times the cost of a butterfly (about its instructions), the larger on a tie.
+template <typename T>
+constexpr int col_threads() {
+  return sizeof(T) == 4 ? 1024 : 512;  // FP64 butterflies of radix 11 and 13 need 256 registers
+}
+inline int radix_cost(int R) { return R % 2 ? R * (R + 6) : 10 * R; }
+inline Shape step_shape(const Factors& f, int csize, int maxt) {
+  Shape s{};
+  const int N = f.n;
+  auto lds = [&](int W) { return ((size_t)root_table_entries(N) + 2 * (size_t)W * N) * csize; };
+  s.W = csize == 8 ? 16 : 8;
+  while (s.W > 1 && lds(s.W) > 160 * 1024) s.W /= 2;
+  const int unit = s.W < 64 ? 64 / s.W : 1;
+  long long best = -1;
+  for (int t = maxt / s.W / unit * unit; t >= unit && 2 * t * s.W >= maxt; t -= unit) {
+    long long cost = 0;
+    for (int i = 0; i < f.nst; ++i) cost += (long long)((N / f.r[i] + t - 1) / t) * radix_cost(f.r[i]);
+    cost *= t;
+    if (best < 0 || cost < best) {
+      best = cost;
+      s.TT = t;
+    }
+  }
+  // small lines: no more threads than the widest stage has butterflies
+  int nb = 0;
+  for (int i = 0; i < f.nst; ++i) nb = nb > N / f.r[i] ? nb : N / f.r[i];
+  if (s.TT > nb) s.TT = (nb + unit - 1) / unit * unit;
+  s.lds = lds(s.W);
+  return s;
+}
+
+// root table into LDS; the line buffers follow it
+template <typename T>
+__device__ __forceinline__ cpx<T>* stage_table(cpx<T>* tw, const cpx<T>* __restrict__ tw_g, int N) {
+  const int nt = (int)root_table_entries(N);
+  for (int i = threadIdx.x; i < nt; i += blockDim.x) tw[i] = tw_g[i];
+  __syncthreads();
+  return tw + nt;
+}
+
+// ---------------------------------------------------------------------------
+// Column passes of the step (the fields of the tuned kernels' passes).
+// z inverse: A fields 0 U1, 1 U2, 2 U3, 3 dz U1, 4 dz U2, 5+2s Phi_s, 6+2s dz Phi_s.
+// ---------------------------------------------------------------------------
+template <typename T>
+__global__ void __launch_bounds__(col_threads<T>())
+k_z_inverse_step(const cpx<T>* __restrict__ st, cpx<T>* __restrict__ abuf, const cpx<T>* __restrict__ tw_g,
+                 const SlotDev* __restrict__ slots, Geom g, Factors fz, int W, int TT, int shift, T scale) {
+  extern __shared__ char lds_raw[];
+  const int slot = blockIdx.z;
+  if (!slots[slot].active) return;
+  const int N = g.N, M = g.M;
+  cpx<T>* tw = reinterpret_cast<cpx<T>*>(lds_raw);
+  cpx<T>* b0 = stage_table(tw, tw_g, N);
+  cpx<T>* b1 = b0 + (size_t)W * N;
+  const int c = threadIdx.x % W, j = threadIdx.x / W;
+  const int kx = blockIdx.x * W + c, kyc = blockIdx.y;
+  const bool valid = kx < g.KX;
+  const int ky = kyc <= g.K ? kyc : kyc - M;
+  const cpx<T>* sbase = st + (long long)slot * g.F * g.st_field + (long long)kyc * g.PX + kx;
+  cpx<T>* abase = abuf + (long long)slot * g.FA * g.a_field + (long long)kyc * g.PX + kx;
+  const long long row = (long long)M * g.PX;  // state and A rows are this far apart along z
+  for (int f = 0; f < g.F; ++f) {
+    const int out = f < 3 ? f : 5 + 2 * (f - 3), dout = f < 2 ? 3 + f : f == 2 ? -1 : out + 1;
+    const cpx<T>* p = sbase + (long long)f * g.st_field;
+    for (int d = 0; d < (dout < 0 ? 1 : 2); ++d) {
+      cpx<T>* q = abase + (long long)(d ? dout : out) * g.a_field;
+      fft_io<true, T>(
+          [&](int n) {
+            const int kz = wave(n, N), kc = compact(kz, g.K, M);
+            cpx<T> v = {T(0), T(0)};
+            // only retained modes are read: the stage inputs hold nothing defined outside a sphere
+            if (valid && kc >= 0 && retained(g, kx, ky, kz)) {
+              v = scale * p[kc * row];
+              if (d) v = mul_is(v, T(kz));
+              if (shift) v = cmul(v, shift_of(tw, N, kz));
+            }
+            return v;
+          },
+          [&](int n, cpx<T> v) {
+            if (valid) q[n * row] = v;
+          },
+          b0, b1, fz, W, c, j, TT, tw);
+    }
+  }
+}
+
+// y inverse: B fields 0 u1, 1 u2, 2 u3, 3 omega1 = dy u3 - dz u2, 4 dz u1, 5 dy u1, then
+// 6+3s phi_s, 7+3s dy phi_s, 8+3s dz phi_s.
+template <typename T>
+__global__ void __launch_bounds__(col_threads<T>())
+k_y_inverse_step(const cpx<T>* __restrict__ abuf, cpx<T>* __restrict__ bbuf, const cpx<T>* __restrict__ tw_g,
+                 const SlotDev* __restrict__ slots, Geom g, Factors fy, int W, int TT, int shift) {
+  extern __shared__ char lds_raw[];
+  const int slot = blockIdx.z;
+  if (!slots[slot].active) return;
+  const int N = g.N, M = g.M;
+  cpx<T>* tw = reinterpret_cast<cpx<T>*>(lds_raw);
+  cpx<T>* b0 = stage_table(tw, tw_g, N);
+  cpx<T>* b1 = b0 + (size_t)W * N;
+  const int c = threadIdx.x % W, j = threadIdx.x / W;
+  const int kx = blockIdx.x * W + c, z = blockIdx.y;
+  const bool valid = kx < g.KX;
+  const cpx<T>* abase = abuf + (long long)slot * g.FA * g.a_field + a_row(z, 0, M, g.PX) + kx;
+  cpx<T>* bbase = bbuf + (long long)slot * g.FB * g.b_field + (long long)z * N * g.PX + kx;
+  for (int i = 0; i < g.FB; ++i) {
+    // output o from input f, times i ky with dk, minus input f2; a field and its y derivative in turn
+    int o, f, f2 = -1;
+    bool dk = false;
+    if (i < 6) {
+      o = i == 0 ? 0 : i == 1 ? 5 : i == 2 ? 1 : i == 3 ? 2 : i == 4 ? 3 : 4;
+      f = i < 2 ? 0 : i == 2 ? 1 : i < 5 ? 2 : 3;
+      dk = i == 1 || i == 4;
+      if (i == 4) f2 = 4;
+    } else {
+      const int s = (i - 6) / 3, q = (i - 6) % 3;
+      o = i;
+      f = 5 + 2 * s + (q == 2 ? 1 : 0);
+      dk = q == 1;
+    }
+    const cpx<T>* p = abase + (long long)f * g.a_field;
+    const cpx<T>* p2 = abase + (long long)(f2 < 0 ? f : f2) * g.a_field;
+    cpx<T>* q = bbase + (long long)o * g.b_field;
+    fft_io<true, T>(
+        [&](int n) {
+          const int ky = wave(n, N), kc = compact(ky, g.K, M);
+          cpx<T> v = {T(0), T(0)};
+          if (valid && kc >= 0) {
+            v = p[kc * g.PX];
+            if (dk) v = mul_is(v, T(ky));
+            if (f2 >= 0) v = v - p2[kc * g.PX];
+            if (shift) v = cmul(v, shift_of(tw, N, ky));
+          }
+          return v;
+        },
+        [&](int n, cpx<T> v) {
+          if (valid) q[n * g.PX] = v;
+        },
+        b0, b1, fy, W, c, j, TT, tw);
+  }
+}
+
+// y forward: the first nf B fields -> A (or the kept unshifted product), rows |ky| <= K; shift
+// multiplies by exp(-i pi ky / N).
+template <typename T>
+__global__ void __launch_bounds__(col_threads<T>())
+k_y_forward_step(const cpx<T>* __restrict__ bbuf, cpx<T>* __restrict__ aout, int a_fields,
+                 const cpx<T>* __restrict__ tw_g, const SlotDev* __restrict__ slots, Geom g, Factors fy, int nf, int W,
+                 int TT, int shift) {
+  extern __shared__ char lds_raw[];
+  const int slot = blockIdx.z;
+  if (!slots[slot].active) return;
+  const int N = g.N, M = g.M;
+  cpx<T>* tw = reinterpret_cast<cpx<T>*>(lds_raw);
+  cpx<T>* b0 = stage_table(tw, tw_g, N);
+  cpx<T>* b1 = b0 + (size_t)W * N;
+  const int c = threadIdx.x % W, j = threadIdx.x / W;
+  const int kx = blockIdx.x * W + c, z = blockIdx.y;
+  const bool valid = kx < g.KX;
+  const cpx<T>* bbase = bbuf + (long long)slot * g.FB * g.b_field + (long long)z * N * g.PX + kx;
+  cpx<T>* obase = aout + (long long)slot * a_fields * g.a_field + a_row(z, 0, M, g.PX) + kx;
+  for (int f = 0; f < nf; ++f) {
+    const cpx<T>* p = bbase + (long long)f * g.b_field;
+    cpx<T>* q = obase + (long long)f * g.a_field;
+    fft_io<false, T>([&](int n) { return valid ? p[n * g.PX] : cpx<T>{T(0), T(0)}; },
+                     [&](int n, cpx<T> v) {
+                       const int ky = wave(n, N), kc = compact(ky, g.K, M);
+                       if (!valid || kc < 0) return;
+                       if (shift) v = cmul(v, conj(shift_of(tw, N, ky)));
+                       q[kc * g.PX] = v;
+                     },
+                     b0, b1, fy, W, c, j, TT, tw);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -281,42 +607,6 @@ k_y_inverse(const cpx<T>* __restrict__ abuf, cpx<T>* __restrict__ bbuf, const cp
     const cpx<T>* res = fft<true>(b0, b1, fy, W, c, j, TT, tw);
     if (valid)
       for (int n = j; n < N; n += TT) bbase[(long long)o * g.b_field + (long long)n * g.PX + kx] = res[n * W + c];
-    __syncthreads();
-  }
-}
-
-// ---------------------------------------------------------------------------
-// y forward: the first nf B fields along y (all N positions) at fixed z -> A (or the kept
-// unshifted product), rows |ky| <= K; shift multiplies by exp(-i pi ky / N).
-// ---------------------------------------------------------------------------
-template <typename T>
-__global__ void __launch_bounds__(1024)
-k_y_forward(const cpx<T>* __restrict__ bbuf, cpx<T>* __restrict__ aout, int a_fields, const cpx<T>* __restrict__ tw,
-            const SlotDev* __restrict__ slots, Geom g, Factors fy, int nf, int W, int TT, int shift) {
-  extern __shared__ char lds_raw[];
-  cpx<T>* b0 = reinterpret_cast<cpx<T>*>(lds_raw);
-  cpx<T>* b1 = b0 + (size_t)W * g.N;
-  const int slot = blockIdx.z;
-  if (!slots[slot].active) return;
-  const int c = threadIdx.x % W, j = threadIdx.x / W;
-  const int kx = blockIdx.x * W + c, z = blockIdx.y;
-  const bool valid = kx < g.KX;
-  const int N = g.N, M = g.M;
-  const cpx<T>* bbase = bbuf + (long long)slot * g.FB * g.b_field + (long long)z * N * g.PX;
-  cpx<T>* obase = aout + (long long)slot * a_fields * g.a_field;
-  for (int f = 0; f < nf; ++f) {
-    for (int n = j; n < N; n += TT)
-      b0[n * W + c] = valid ? bbase[(long long)f * g.b_field + (long long)n * g.PX + kx] : cpx<T>{T(0), T(0)};
-    __syncthreads();
-    const cpx<T>* res = fft<false>(b0, b1, fy, W, c, j, TT, tw);
-    if (valid)
-      for (int n = j; n < N; n += TT) {
-        const int ky = wave(n, N), kc = compact(ky, g.K, M);
-        if (kc < 0) continue;
-        cpx<T> v = res[n * W + c];
-        if (shift) v = cmul(v, conj(shift_of(tw, N, ky)));
-        obase[(long long)f * g.a_field + a_row(z, kc, M, g.PX) + kx] = v;
-      }
     __syncthreads();
   }
 }
@@ -455,7 +745,7 @@ k_x_pass(cpx<T>* __restrict__ bbuf, const cpx<T>* __restrict__ tw_g, const SlotD
       }
     }
     WaveSync::sync();
-    const cpx<T>* r = fft<false, WaveSync>(b0, b1, fx, 1, 0, j, 64, tw);
+    const cpx<T>* r = fft_in<false, WaveSync, T>([&](int n) { return b0[n]; }, b1, b0, fx, 1, 0, j, 64, tw);
     if (job == 3) {
       for (int k = j; k <= K; k += 64) {
         const cpx<T> zk = r[k], zc = conj(r[(N - k) % N]);
@@ -646,9 +936,10 @@ inline Shape zf_shape(int N, int csize) {
   Shape s{};
   s.TT = csize == 8 ? 64 : 128;
   if (s.TT > N / 2) s.TT = N / 2;
+  auto lds = [&](int W) { return ((size_t)root_table_entries(N) + 2 * (size_t)W * N) * csize; };
   s.W = csize == 8 ? 8 : 4;
-  while (s.W > 1 && 2 * (size_t)s.W * N * csize > 150 * 1024) s.W /= 2;
-  s.lds = 2 * (size_t)s.W * N * csize;
+  while (s.W > 1 && lds(s.W) > 160 * 1024) s.W /= 2;
+  s.lds = lds(s.W);
   return s;
 }
 inline int zf_positions(int N, int TT) { return (N + TT - 1) / TT; }
@@ -659,14 +950,15 @@ inline int zf_positions(int N, int TT) { return (N + TT - 1) / TT; }
 template <typename T, int P>
 __global__ void __launch_bounds__(512)
 k_z_forward_update(const cpx<T>* __restrict__ abuf, const cpx<T>* __restrict__ akeep, GStage<T> sa,
-                   const cpx<T>* __restrict__ tw, const SlotDev* __restrict__ slots, const DynDev* __restrict__ dyn,
+                   const cpx<T>* __restrict__ tw_g, const SlotDev* __restrict__ slots, const DynDev* __restrict__ dyn,
                    Geom g, Factors fz, int W, int TT) {
   extern __shared__ char lds_raw[];
-  cpx<T>* b0 = reinterpret_cast<cpx<T>*>(lds_raw);
-  cpx<T>* b1 = b0 + (size_t)W * g.N;
   const int slot = blockIdx.z;
   const SlotDev& sp = slots[slot];
   if (!sp.active) return;
+  cpx<T>* tw = reinterpret_cast<cpx<T>*>(lds_raw);
+  cpx<T>* b0 = stage_table(tw, tw_g, g.N);
+  cpx<T>* b1 = b0 + (size_t)W * g.N;
   const int c = threadIdx.x % W, j = threadIdx.x / W;
   const int kx = blockIdx.x * W + c, kyc = blockIdx.y;
   const bool valid = kx < g.KX;
@@ -702,10 +994,9 @@ k_z_forward_update(const cpx<T>* __restrict__ abuf, const cpx<T>* __restrict__ a
     const int fi = t / per, half = t % per;
     const int f = fi < S ? 3 + fi : fi - S;  // A field: scalar fi, or velocity component fi - S
     const cpx<T>* src = (half ? kslot : aslot) + (long long)f * g.a_field;
-    for (int n = j; n < N; n += TT)
-      b0[n * W + c] = valid ? src[a_row(n, kyc, M, g.PX) + kx] : cpx<T>{T(0), T(0)};
-    __syncthreads();
-    const cpx<T>* r = fft<false>(b0, b1, fz, W, c, j, TT, tw);
+    const cpx<T>* r = fft_in<false, BlockSync, T>(
+        [&](int n) { return valid ? src[a_row(n, kyc, M, g.PX) + kx] : cpx<T>{T(0), T(0)}; }, b0, b1, fz, W, c, j, TT,
+        tw);
 #pragma unroll
     for (int m = 0; m < P; ++m) {
       const int n = j + TT * m;
