@@ -2046,67 +2046,144 @@ __device__ __forceinline__ int isqrt_floor(long long v) {
   return (int)r;
 }
 
-template <typename T>
-__global__ void __launch_bounds__(256)
+// Blocks of the shell sums per slot, for m^2 rows of the state.
+inline int shell_blocks(int m) {
+  const int n = m * m / 4;
+  return n < 1 ? 1 : n > 2048 ? 2048 : n;
+}
+
+// Shell sums of the rows blockIdx.x, blockIdx.x + gridDim.x, .. of a slot, one wavefront per
+// block.  Along a row the shell index never falls and rises by at most one per kx, so the modes of
+// a shell are a run of lanes: a segmented scan sums each run, and its last lane adds the sums to
+// the wave's own table of shells in LDS.  Every state value is read once, in whole rows, where a
+// block per shell touched each row once for every shell that crosses it (512^3, two scalars:
+// 3.13 ms).  part (shell_blocks tables per slot, part_stride doubles from slot to slot) lies in
+// the transform buffers; k_shell_reduce adds the tables in a fixed order.
+template <typename T, int S>
+__global__ void __launch_bounds__(64)
 k_shell_sums(const cpx<T>* __restrict__ st, const SlotDev* __restrict__ slots, Geom g, double* __restrict__ part,
-             int ns) {
-  constexpr int MAXQ = 2 + 3 * kMaxScalars;
-  __shared__ double red[MAXQ][256];
-  const int sh = blockIdx.x;
-  const int slot = blockIdx.y;
+             long long part_stride, int ns) {
+  constexpr int Q = 2 + 3 * S;
+  extern __shared__ double hist[];
+  const int slot = blockIdx.y, lane = threadIdx.x;
   const SlotDev& sp = slots[slot];
-  const int S = g.S, Q = shell_quantities(S), K = g.K, M = g.M;
-  const long long lo = sh == 0 ? 0 : (long long)sh * sh - sh + 1;  // nint(|k|) = sh <=> lo <= |k|^2 <= hi
-  const long long hi = (long long)sh * sh + sh;
-  int R = isqrt_floor(hi);
-  if (R > K) R = K;
-  const int span = 2 * R + 1;
-  double acc[MAXQ];
-#pragma unroll
-  for (int q = 0; q < MAXQ; ++q) acc[q] = 0.0;
+  const int K = g.K, M = g.M;
+  for (int i = lane; i < ns * Q; i += 64) hist[i] = 0.0;
+  WaveSync::sync();
   const cpx<T>* base = st + (long long)slot * g.F * g.st_field;
-  for (int p = threadIdx.x; p < span * span; p += 256) {
-    const int kz = p / span - R, ky = p % span - R;
-    const long long r2 = (long long)kz * kz + (long long)ky * ky;
-    if (r2 > hi) continue;
-    int x0 = lo - r2 > 0 ? isqrt_floor(lo - r2 - 1) + 1 : 0;  // smallest kx with kx^2 >= lo - r2
-    int x1 = isqrt_floor(hi - r2);
-    if (x1 > K) x1 = K;
-    const int kzc = kz >= 0 ? kz : kz + M, kyc = ky >= 0 ? ky : ky + M;
-    const long long row = st_row(kzc, kyc, M, g.PX);
-    for (int kx = x0; kx <= x1; ++kx) {
-      const long long o = row + kx;
-      const double w = kx == 0 ? 1.0 : 2.0;
-      const double k2 = double(r2) + double(kx) * kx;
-      const cpx<T> a = base[o], b = base[o + g.st_field], c = base[o + 2 * g.st_field];
-      const double u1r = a.x, u1i = a.y, u2r = b.x, u2i = b.y, u3r = c.x, u3i = c.y;
-      const double uu = u1r * u1r + u1i * u1i + u2r * u2r + u2i * u2i + u3r * u3r + u3i * u3i;
-      const double kur = kx * u1r + ky * u2r + kz * u3r, kui = kx * u1i + ky * u2i + kz * u3i;
-      acc[0] += 0.5 * w * uu;
-      acc[1] += w * (k2 * uu + kur * kur + kui * kui);
+  for (int r = blockIdx.x; r < M * M; r += gridDim.x) {
+    const int kz = wave_of_compact(r / M, K, M), ky = wave_of_compact(r % M, K, M);
+    const int r2 = kz * kz + ky * ky;
+    const cpx<T>* row = base + (long long)r * g.PX;
+    for (int x0 = 0; x0 < g.KX; x0 += 64) {
+      const int kx = x0 + lane;
+      const bool in = kx < g.KX;
+      double v[Q];
 #pragma unroll
-      for (int s = 0; s < kMaxScalars; ++s) {
-        if (s >= S) break;
-        const cpx<T> f = base[o + (3 + s) * g.st_field];
-        const double fr = f.x, fi = f.y, ff = fr * fr + fi * fi;
-        const double gur = sp.g[s][0] * u1r + sp.g[s][1] * u2r + sp.g[s][2] * u3r;
-        const double gui = sp.g[s][0] * u1i + sp.g[s][1] * u2i + sp.g[s][2] * u3i;
-        acc[2 + 3 * s] += 0.5 * w * ff;
-        acc[3 + 3 * s] += w * k2 * ff;
-        acc[4 + 3 * s] += w * (fr * gur + fi * gui);
+      for (int q = 0; q < Q; ++q) v[q] = 0.0;
+      int sh = 0x7fffffff;  // lanes past the row: a run of their own, never added
+      if (in) {
+        const int k2i = r2 + kx * kx;
+        int fl = (int)__fsqrt_rn((float)k2i);  // floor(|k|) to within one (|k|^2 < 2^24)
+        fl -= fl * fl > k2i;
+        fl += (fl + 1) * (fl + 1) <= k2i;
+        sh = k2i > fl * fl + fl ? fl + 1 : fl;  // nint(|k|)
+        const double w = kx == 0 ? 1.0 : 2.0;
+        const double k2 = double(k2i);
+        const cpx<T> a = row[kx], b = row[kx + g.st_field], c = row[kx + 2 * g.st_field];
+        const double u1r = a.x, u1i = a.y, u2r = b.x, u2i = b.y, u3r = c.x, u3i = c.y;
+        const double uu = u1r * u1r + u1i * u1i + u2r * u2r + u2i * u2i + u3r * u3r + u3i * u3i;
+        const double kur = kx * u1r + ky * u2r + kz * u3r, kui = kx * u1i + ky * u2i + kz * u3i;
+        v[0] = 0.5 * w * uu;
+        v[1] = w * (k2 * uu + kur * kur + kui * kui);
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+          const cpx<T> f = row[kx + (3 + s) * g.st_field];
+          const double fr = f.x, fi = f.y, ff = fr * fr + fi * fi;
+          const double gur = sp.g[s][0] * u1r + sp.g[s][1] * u2r + sp.g[s][2] * u3r;
+          const double gui = sp.g[s][0] * u1i + sp.g[s][1] * u2i + sp.g[s][2] * u3i;
+          v[2 + 3 * s] = 0.5 * w * ff;
+          v[3 + 3 * s] = w * k2 * ff;
+          v[4 + 3 * s] = w * (fr * gur + fi * gui);
+        }
       }
+#pragma unroll
+      for (int d = 1; d < 64; d <<= 1) {
+        const bool same = __shfl_up(sh, d) == sh && lane >= d;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+          const double o = __shfl_up(v[q], d);
+          v[q] += same ? o : 0.0;
+        }
+      }
+      const bool last = __shfl_down(sh, 1) != sh || lane == 63;
+      if (in && last) {
+#pragma unroll
+        for (int q = 0; q < Q; ++q) hist[sh * Q + q] += v[q];
+      }
+      WaveSync::sync();
     }
   }
-#pragma unroll
-  for (int q = 0; q < MAXQ; ++q)
-    if (q < Q) red[q][threadIdx.x] = acc[q];
+  double* o = part + slot * part_stride + (long long)blockIdx.x * ns * Q;
+  for (int i = lane; i < ns * Q; i += 64) o[i] = hist[i];
+}
+
+// Sum over the block's 256 threads, in a fixed order, of get(i) over i < n.
+template <class Get>
+__device__ __forceinline__ double block_total(int n, double* red, Get&& get) {
+  double v = 0.0;
+  for (int i = threadIdx.x; i < n; i += 256) v += get(i);
+  red[threadIdx.x] = v;
   __syncthreads();
   for (int o = 128; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o)
-      for (int q = 0; q < Q; ++q) red[q][threadIdx.x] += red[q][threadIdx.x + o];
+    if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
     __syncthreads();
   }
-  if ((int)threadIdx.x < Q) part[((long long)slot * ns + sh) * Q + threadIdx.x] = red[threadIdx.x][0];
+  v = red[0];
+  __syncthreads();
+  return v;
+}
+
+// shells[slot][shell][quantity] from the nb tables of a slot
+static __global__ void __launch_bounds__(256)
+k_shell_reduce(const double* __restrict__ part, long long part_stride, int nb, Geom g, int ns,
+               double* __restrict__ shells) {
+  __shared__ double red[256];
+  const int sh = blockIdx.x, slot = blockIdx.y, Q = shell_quantities(g.S);
+  const double* p = part + slot * part_stride + (long long)sh * Q;
+  for (int q = 0; q < Q; ++q) {
+    const double v = block_total(nb, red, [&](int b) { return p[(long long)b * ns * Q + q]; });
+    if (threadIdx.x == 0) shells[((long long)slot * ns + sh) * Q + q] = v;
+  }
+}
+
+// Launches both into `shells`; scratch: the transform buffer B, free until the moments' passes.
+template <typename T>
+void shell_sums(const Ctx& x, const cpx<T>* st, double* shells, hipStream_t s) {
+  const Geom& g = x.g;
+  const int nb = shell_blocks(g.M), Q = shell_quantities(g.S);
+  double* part = static_cast<double*>(x.bbuf);
+  const long long stride = (long long)g.FB * g.b_field * (long long)(sizeof(cpx<T>) / sizeof(double));
+  const dim3 grid(nb, g.batch);
+  const size_t lds = (size_t)g.ns * Q * sizeof(double);
+  switch (g.S) {
+    case 0: k_shell_sums<T, 0><<<grid, 64, lds, s>>>(st, x.slots, g, part, stride, g.ns); break;
+    case 1: k_shell_sums<T, 1><<<grid, 64, lds, s>>>(st, x.slots, g, part, stride, g.ns); break;
+    case 2: k_shell_sums<T, 2><<<grid, 64, lds, s>>>(st, x.slots, g, part, stride, g.ns); break;
+    case 3: k_shell_sums<T, 3><<<grid, 64, lds, s>>>(st, x.slots, g, part, stride, g.ns); break;
+    default: k_shell_sums<T, 4><<<grid, 64, lds, s>>>(st, x.slots, g, part, stride, g.ns); break;
+  }
+  k_shell_reduce<<<dim3(g.ns, g.batch), 256, 0, s>>>(part, stride, nb, g, g.ns, shells);
+}
+// the shell table of the largest grids exceeds the default limit of dynamic LDS
+template <typename T>
+void allow_shell_lds() {
+  auto allow = [](const void* f) { (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024); };
+  allow(reinterpret_cast<const void*>(&k_shell_sums<T, 0>));
+  allow(reinterpret_cast<const void*>(&k_shell_sums<T, 1>));
+  allow(reinterpret_cast<const void*>(&k_shell_sums<T, 2>));
+  allow(reinterpret_cast<const void*>(&k_shell_sums<T, 3>));
+  allow(reinterpret_cast<const void*>(&k_shell_sums<T, 4>));
 }
 
 // Inverse z transform of up to 8 derived fields i k_axis * (field) of the state
@@ -2117,11 +2194,16 @@ struct DerivSpec {
   int axis[8];
 };
 
+// column blocks of the statistics: eight elements per thread at every size (their values do not
+// follow the step's schedules)
 template <int N, typename T>
-__global__ void PSDNS_COL_BOUNDS(Cfg<N, T>::COL_THREADS)
+using StatCol = ColCfg<N, T, 8, row_bytes<N>(0, PSDNS_COL_BYTES)>;
+
+template <int N, typename T>
+__global__ void PSDNS_COL_BOUNDS(StatCol<N, T>::THREADS)
 k_stats_z(const cpx<T>* __restrict__ st, cpx<T>* __restrict__ abuf, const cpx<T>* __restrict__ tw_g, Geom g,
           DerivSpec spec) {
-  using C = Cfg<N, T>;
+  using C = StatCol<N, T>;
   constexpr int W = C::W, E = C::EC, TT = C::TC;
   constexpr int K = (N - 1) / 3, M = 2 * K + 1;
   __shared__ cpx<T> smem[W * N];
@@ -2159,10 +2241,10 @@ k_stats_z(const cpx<T>* __restrict__ st, cpx<T>* __restrict__ abuf, const cpx<T>
 
 // Plain inverse y transform of nf fields (A layout -> B layout).
 template <int N, typename T>
-__global__ void PSDNS_COL_BOUNDS(Cfg<N, T>::COL_THREADS)
+__global__ void PSDNS_COL_BOUNDS(StatCol<N, T>::THREADS)
 k_stats_y(const cpx<T>* __restrict__ abuf, cpx<T>* __restrict__ bbuf, const cpx<T>* __restrict__ tw_g, Geom g,
           int nf) {
-  using C = Cfg<N, T>;
+  using C = StatCol<N, T>;
   constexpr int W = C::W, E = C::EC, TT = C::TC;
   constexpr int K = (N - 1) / 3, M = 2 * K + 1;
   __shared__ cpx<T> smem[W * N];
@@ -2298,87 +2380,92 @@ k_spectra_finalize(const double* __restrict__ shells, const double* __restrict__
                    int nbm, const SlotDev* __restrict__ slots, Geom g, int ns, int flags, double* __restrict__ out,
                    int rec) {
   const int slot = blockIdx.x;
+  __shared__ double red[256];
   const SlotDev& sp = slots[slot];
-  const int S = g.S, Q = shell_quantities(S);
+  const int S = g.S, Q = shell_quantities(S), tid = threadIdx.x;
   double* o = out + (long long)slot * rec;
   const double nan = __builtin_nan("");
   const double n3 = double(g.N) * g.N * g.N, n6 = n3 * n3;
   const int base = ns * (1 + S);
   const int pb = base + 8 + 4 * S;
-  if (threadIdx.x == 0) {
-    for (int i = 0; i < rec; ++i) o[i] = nan;
-  }
+  for (int i = tid; i < rec; i += 256) o[i] = nan;
   __syncthreads();
-  if ((flags & 1) && threadIdx.x == 0) {
+  if (flags & 1) {
     const double* sh = shells + (long long)slot * ns * Q;
-    double K = 0.0, diss = 0.0;
-    for (int s = 0; s < ns; ++s) {
-      o[s] = sh[s * Q + 0] / n6;
-      K += sh[s * Q + 0];
-      diss += sh[s * Q + 1];
+    for (int i = tid; i < base; i += 256) {
+      const int f = i / ns, h = i % ns;  // E (f = 0) or E_phi of scalar f - 1
+      o[i] = sh[h * Q + (f == 0 ? 0 : 2 + 3 * (f - 1))] / n6;
     }
-    K /= n6;
-    const double eps = sp.nu * diss / n6;
+    const double K = block_total(ns, red, [&](int h) { return sh[h * Q + 0]; }) / n6;
+    const double eps = sp.nu * block_total(ns, red, [&](int h) { return sh[h * Q + 1]; }) / n6;
     const double urms = sqrt(2.0 * K / 3.0);
-    o[base + 0] = K;
-    o[base + 1] = eps;
-    o[base + 2] = urms;
-    if (eps > 0.0) {
-      const double lam = urms * sqrt(15.0 * sp.nu / eps);
-      o[base + 3] = lam;
-      o[base + 4] = lam * urms / sp.nu;
-      o[base + 5] = pow(sp.nu * sp.nu * sp.nu / eps, 0.25);
-      o[base + 6] = urms * urms * urms / eps;
-      o[base + 7] = urms > 0.0 ? (urms * urms * urms / eps) / urms : nan;
+    if (tid == 0) {
+      o[base + 0] = K;
+      o[base + 1] = eps;
+      o[base + 2] = urms;
+      if (eps > 0.0) {
+        const double lam = urms * sqrt(15.0 * sp.nu / eps);
+        o[base + 3] = lam;
+        o[base + 4] = lam * urms / sp.nu;
+        o[base + 5] = pow(sp.nu * sp.nu * sp.nu / eps, 0.25);
+        o[base + 6] = urms * urms * urms / eps;
+        o[base + 7] = urms > 0.0 ? (urms * urms * urms / eps) / urms : nan;
+      }
     }
     for (int s = 0; s < S; ++s) {
-      double var = 0.0, chi = 0.0, prod = 0.0;
-      for (int h = 0; h < ns; ++h) {
-        o[ns * (1 + s) + h] = sh[h * Q + 2 + 3 * s] / n6;
-        var += sh[h * Q + 2 + 3 * s];
-        chi += sh[h * Q + 3 + 3 * s];
-        prod += sh[h * Q + 4 + 3 * s];
-      }
+      const double var = block_total(ns, red, [&](int h) { return sh[h * Q + 2 + 3 * s]; });
+      const double chi = block_total(ns, red, [&](int h) { return sh[h * Q + 3 + 3 * s]; });
+      const double prod = block_total(ns, red, [&](int h) { return sh[h * Q + 4 + 3 * s]; });
       const double d = sp.diff[3 + s];
-      o[base + 8 + 4 * s + 0] = 2.0 * var / n6;
-      o[base + 8 + 4 * s + 1] = 2.0 * d * chi / n6;
-      o[base + 8 + 4 * s + 2] = -2.0 * prod / n6;
-      o[base + 8 + 4 * s + 3] = (-2.0 * prod / n6) / (2.0 * d * chi / n6);
+      if (tid == 0) {
+        o[base + 8 + 4 * s + 0] = 2.0 * var / n6;
+        o[base + 8 + 4 * s + 1] = 2.0 * d * chi / n6;
+        o[base + 8 + 4 * s + 2] = -2.0 * prod / n6;
+        o[base + 8 + 4 * s + 3] = (-2.0 * prod / n6) / (2.0 * d * chi / n6);
+      }
     }
   }
-  if ((flags & 2) && threadIdx.x == 0) {
+  if (flags & 2) {
     // first sweep: fields u1 u2 u3 | du1/dx1 du2/dx2 (moments of the last two) + max
     // second sweep: du3/dx3, dphi_s/dx2 (moments of all)
-    double m1[2][3] = {{0, 0, 0}, {0, 0, 0}}, mx = 0.0;
-    double m2[1 + kMaxScalars][3] = {};
-    const int r1 = 3 * 2 + 1, r2 = 3 * (1 + S) + 1;
-    for (int b = 0; b < nbm; ++b) {
-      const double* p = mom1 + ((long long)slot * nbm + b) * (3 * 6 + 1);
-      for (int f = 0; f < 2; ++f)
-        for (int r = 0; r < 3; ++r) m1[f][r] += p[3 * f + r];
-      const double v = p[r1 - 1];
+    const double* p1 = mom1 + (long long)slot * nbm * (3 * 6 + 1);
+    const double* p2 = mom2 + (long long)slot * nbm * (3 * 6 + 1);
+    auto total = [&](const double* p, int q) {
+      return block_total(nbm, red, [&](int b) { return p[(long long)b * (3 * 6 + 1) + q]; });
+    };
+    for (int i = 0; i < 3 + S; ++i) {
+      const double* p = i < 2 ? p1 : p2;
+      const int f = i < 2 ? i : i - 2;
+      const double a2 = total(p, 3 * f) / n3, a3 = total(p, 3 * f + 1) / n3, a4 = total(p, 3 * f + 2) / n3;
+      if (tid != 0) continue;
+      const double skew = a2 > 0 ? a3 / pow(a2, 1.5) : nan, flat = a2 > 0 ? a4 / (a2 * a2) : nan;
+      if (i < 3) {
+        o[pb + i] = a2;
+        o[pb + 3 + i] = a3;
+        o[pb + 6 + i] = a4;
+        o[pb + 9 + i] = skew;
+        o[pb + 12 + i] = flat;
+      } else {
+        o[pb + 16 + 3 * (i - 3)] = a2;
+        o[pb + 17 + 3 * (i - 3)] = skew;
+        o[pb + 18 + 3 * (i - 3)] = flat;
+      }
+    }
+    double mx = 0.0;
+    for (int b = tid; b < nbm; b += 256) {
+      const double v = p1[(long long)b * (3 * 6 + 1) + 6];
       mx = (v > mx || v != v) ? v : mx;
-      const double* q = mom2 + ((long long)slot * nbm + b) * (3 * 6 + 1);
-      for (int f = 0; f < 1 + S; ++f)
-        for (int r = 0; r < 3; ++r) m2[f][r] += q[3 * f + r];
-      (void)r2;
     }
-    const double* mm[3] = {m1[0], m1[1], m2[0]};
-    for (int i = 0; i < 3; ++i) {
-      const double a2 = mm[i][0] / n3, a3 = mm[i][1] / n3, a4 = mm[i][2] / n3;
-      o[pb + i] = a2;
-      o[pb + 3 + i] = a3;
-      o[pb + 6 + i] = a4;
-      o[pb + 9 + i] = a2 > 0 ? a3 / pow(a2, 1.5) : nan;
-      o[pb + 12 + i] = a2 > 0 ? a4 / (a2 * a2) : nan;
+    red[tid] = mx;
+    __syncthreads();
+    for (int h = 128; h > 0; h >>= 1) {
+      if (tid < h) {
+        const double a = red[tid], b = red[tid + h];
+        red[tid] = (b > a || b != b) ? b : a;
+      }
+      __syncthreads();
     }
-    o[pb + 15] = mx;
-    for (int s = 0; s < S; ++s) {
-      const double a2 = m2[1 + s][0] / n3, a3 = m2[1 + s][1] / n3, a4 = m2[1 + s][2] / n3;
-      o[pb + 16 + 3 * s] = a2;
-      o[pb + 17 + 3 * s] = a2 > 0 ? a3 / pow(a2, 1.5) : nan;
-      o[pb + 18 + 3 * s] = a2 > 0 ? a4 / (a2 * a2) : nan;
-    }
+    if (tid == 0) o[pb + 15] = red[0];
   }
 }
 
@@ -2676,9 +2763,10 @@ struct Engine {
     double* shells = x.stat;
     double* mom1 = shells + (long long)g.batch * ns * Q;
     double* mom2 = mom1 + (long long)g.batch * x.nbm * (3 * 6 + 1);
-    const int ntile = (g.KX + C::W - 1) / C::W;
+    using CS = StatCol<N, T>;
+    const int ntile = (g.KX + CS::W - 1) / CS::W;
     TimedLaunch tl(x.timer, KID_AUX, s);
-    if (flags & 1) k_shell_sums<T><<<dim3(ns, g.batch), 256, 0, s>>>(st, x.slots, g, shells, ns);
+    if (flags & 1) shell_sums(x, st, shells, s);
     if (flags & 2) {
       DerivSpec d1{};
       d1.nf = 5;
@@ -2687,8 +2775,8 @@ struct Engine {
         d1.field[i] = f1[i];
         d1.axis[i] = a1[i];
       }
-      k_stats_z<N, T><<<dim3(ntile, g.M, g.batch), C::COL_THREADS, 0, s>>>(st, A, tw, g, d1);
-      k_stats_y<N, T><<<dim3(ntile, N, g.batch), C::COL_THREADS, 0, s>>>(A, B, tw, g, 5);
+      k_stats_z<N, T><<<dim3(ntile, g.M, g.batch), CS::THREADS, 0, s>>>(st, A, tw, g, d1);
+      k_stats_y<N, T><<<dim3(ntile, N, g.batch), CS::THREADS, 0, s>>>(A, B, tw, g, 5);
       k_x_moments<N, T><<<dim3(x.nbm, g.batch), C::X_THREADS, 0, s>>>(B, tw, g, 5, 3, 1, mom1);
       DerivSpec d2{};
       d2.nf = 1 + g.S;
@@ -2698,8 +2786,8 @@ struct Engine {
         d2.field[1 + i] = 3 + i;
         d2.axis[1 + i] = 2;
       }
-      k_stats_z<N, T><<<dim3(ntile, g.M, g.batch), C::COL_THREADS, 0, s>>>(st, A, tw, g, d2);
-      k_stats_y<N, T><<<dim3(ntile, N, g.batch), C::COL_THREADS, 0, s>>>(A, B, tw, g, 1 + g.S);
+      k_stats_z<N, T><<<dim3(ntile, g.M, g.batch), CS::THREADS, 0, s>>>(st, A, tw, g, d2);
+      k_stats_y<N, T><<<dim3(ntile, N, g.batch), CS::THREADS, 0, s>>>(A, B, tw, g, 1 + g.S);
       k_x_moments<N, T><<<dim3(x.nbm, g.batch), C::X_THREADS, 0, s>>>(B, tw, g, 1 + g.S, 0, 0, mom2);
     }
     k_spectra_finalize<<<g.batch, 256, 0, s>>>(shells, mom1, mom2, x.nbm, x.slots, g, ns, flags, out,
@@ -2728,6 +2816,7 @@ struct Engine {
   }
 
   static Ops ops() {
+    allow_shell_lds<T>();
     Ops o{};
     o.nsched = sched_count<N>();
     add_scheds<0, sched_count<N>()>(o);

@@ -234,7 +234,7 @@ struct GEngine {
     double* mom2 = mom1 + (long long)g.batch * x.nbm * (3 * 6 + 1);
     TimedLaunch tl(x.timer, KID_AUX, s);
     const cpx<T>* st = static_cast<const cpx<T>*>(state);
-    if (flags & 1) k_shell_sums<T><<<dim3(ns, g.batch), 256, 0, s>>>(st, x.slots, g, shells, ns);
+    if (flags & 1) shell_sums(x, st, shells, s);
     if (flags & 2) {
       const int t = moment_threads(g);
       const size_t xl = gen::moment_lds_bytes(g.N, (int)sizeof(cpx<T>), t);
@@ -302,6 +302,7 @@ struct GEngine {
 
   static Ops ops() {
     allow_lds();
+    allow_shell_lds<T>();
     Ops o{};
     o.nsched = 1;
     StepSched& d = o.sched[0];
