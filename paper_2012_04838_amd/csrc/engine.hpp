@@ -26,10 +26,10 @@ namespace psdns {
 // Tuning knobs (elements per thread, minimum waves per SIMD for the register
 // allocator; 0 leaves the allocator free).
 #ifndef PSDNS_EC32
-#define PSDNS_EC32 8
+#define PSDNS_EC32 0
 #endif
 #ifndef PSDNS_EC64
-#define PSDNS_EC64 8
+#define PSDNS_EC64 0
 #endif
 #ifndef PSDNS_COL_WAVES
 #define PSDNS_COL_WAVES 0
@@ -75,10 +75,10 @@ namespace psdns {
 
 // elements per thread of the fused z-forward/update/z-inverse pass
 #ifndef PSDNS_EF32
-#define PSDNS_EF32 8
+#define PSDNS_EF32 0
 #endif
 #ifndef PSDNS_EF64
-#define PSDNS_EF64 8
+#define PSDNS_EF64 0
 #endif
 
 // row segment of the z-forward/update pass (both variants), in bytes
@@ -182,6 +182,13 @@ template <int N>
 constexpr int sched_count() {
   return kNumSched;
 }
+// Elements per thread of the column passes in the schedules that take the default: eight, and four
+// on lines of at most 32 points, whose blocks are so small that the length of a thread's chain
+// counts (32^3 FP64: fused z pass 20.2 us against 15.6, y inverse 11.5 against 9.6).
+template <int N>
+constexpr int default_elems(int e) {
+  return e > 0 ? e : (N <= 32 ? 4 : 8);
+}
 template <int N>
 constexpr int row_bytes(int b, int dflt) {
   return b > 0 ? b : (N > 512 ? 64 : dflt);
@@ -191,8 +198,8 @@ template <int N, typename T, int V = 0>
 struct Cfg {
   static constexpr Sched D = kSched[V];
   static constexpr bool F32 = sizeof(T) == 4;
-  using Col = ColCfg<N, T, F32 ? D.ec32 : D.ec64, row_bytes<N>(D.bytes, PSDNS_COL_BYTES)>;
-  using Fused = ColCfg<N, T, F32 ? D.ef32 : D.ef64, row_bytes<N>(F32 ? D.fb32 : D.fb64, F32 ? PSDNS_FB32 : PSDNS_FB64)>;
+  using Col = ColCfg<N, T, default_elems<N>(F32 ? D.ec32 : D.ec64), row_bytes<N>(D.bytes, PSDNS_COL_BYTES)>;
+  using Fused = ColCfg<N, T, default_elems<N>(F32 ? D.ef32 : D.ef64), row_bytes<N>(F32 ? D.fb32 : D.fb64, F32 ? PSDNS_FB32 : PSDNS_FB64)>;
   // columns per block and elements per thread of the column passes (z, y)
   static constexpr int W = Col::W;
   static constexpr int EC = Col::EC;
