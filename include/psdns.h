@@ -330,7 +330,9 @@ psdns_status psdns_use_general_kernels(psdns_plan* plan);
  * selects for each pass the lowest-index schedule within 1% of its fastest (schedules that
  * coincide at a size then resolve to the same choice on every run).  Returns the mean
  * milliseconds of every pass and schedule in host array ms_out[n_schedules *
- * PSDNS_NUM_PASSES] (schedule-major; may be NULL) and the selection in
+ * PSDNS_NUM_PASSES] (schedule-major; may be NULL; where schedule 0 runs the y inverse, the x
+ * pass and the y forward as one pass per plane, at n = 32 and 64, its time is shared out among
+ * the three in the proportion of the fastest separate ones) and the selection in
  * best[PSDNS_NUM_PASSES] (may be NULL).  Leaves `state` and the step records untouched.
  * Synchronises the stream. */
 psdns_status psdns_tune_passes(psdns_plan* plan, const void* state, void* ws, int32_t reps, double* ms_out,

@@ -895,6 +895,20 @@ psdns_status psdns_tune_passes(psdns_plan* plan, const void* state, void* ws, in
   }
   // the lowest-index schedule within 1% of the fastest: schedules whose kernels coincide at
   // this size (or differ within the timing noise) resolve to the same choice on every run
+  if (plan->ops.plane && plan->ops.rhs_mixed && ns > 1) {
+    // schedule 0 of these three passes is one launch, timed as the x pass: its time is shared out
+    // in the proportion of the fastest separate passes, so that all three take it or none does
+    const int three[3] = {kPassYInverse, kPassX, kPassYForward};
+    double apart[3], sum = 0.0;
+    for (int q = 0; q < 3; ++q) {
+      apart[q] = ms[(size_t)kNumPasses + three[q]];
+      for (int i = 2; i < ns; ++i) apart[q] = std::min(apart[q], ms[(size_t)i * kNumPasses + three[q]]);
+      sum += apart[q];
+    }
+    const double whole = ms[kPassX];
+    if (sum > 0.0)
+      for (int q = 0; q < 3; ++q) ms[three[q]] = whole * apart[q] / sum;
+  }
   int32_t pick[kNumPasses];
   for (int p = 0; p < kNumPasses; ++p) {
     double lo = ms[p];

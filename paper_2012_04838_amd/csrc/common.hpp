@@ -173,6 +173,8 @@ struct Ops {
   RhsStageFn rhs_mixed;
   // the stage with the phase-shift dealiasing on the step kernels of this N (null: none)
   RhsStageFn rhs_phase;
+  // schedule 0 of the y inverse, x pass and y forward is one plane pass (rhs_mixed)
+  bool plane;
   void (*init_field)(const Ctx&, void* state, int slot, uint64_t seed, double k_peak, int spectrum, double energy,
                      hipStream_t);
   void (*get_state)(const Ctx&, const void* state, int slot, void* canon, hipStream_t);

@@ -438,8 +438,6 @@ constexpr int kForceParts = 256;
 template <typename T>
 __device__ __forceinline__ void forcing_block(const cpx<T>* __restrict__ sin, const SlotDev& sp, DynDev& dyn,
                                               const Geom& g, int slot, double* red) {
-  // every stage starts a fresh grid maximum (only stage 0's x pass contributes to it)
-  if (threadIdx.x == 0) dyn.umax = 0ull;
   if (sp.forcing != PSDNS_FORCING_POWER) {
     // the hold scheme acts after the last stage only (k_band_hold)
     if (threadIdx.x == 0) dyn.A = 0.0;
@@ -497,6 +495,7 @@ static __device__ __forceinline__ void step_dt(DynDev& d, const Geom& g, double 
   d.t += dt;
   d.steps += 1;
   d.flags = fl;
+  d.umax = 0ull;  // the next step's stage 0 starts a fresh grid maximum
 }
 
 // the same as launches of their own, for the general kernels
@@ -1045,6 +1044,247 @@ k_x_pass(cpx<T>* __restrict__ bbuf, const cpx<T>* __restrict__ tw_g, const SlotD
       __syncthreads();
     }
     if (threadIdx.x == 0) atomicMax(&dyn[slot].umax, (unsigned long long)__double_as_longlong(red[0]));
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Plane pass (N = 32 and 64, 2/3 rule): the y inverse, the x pass and the y forward of one z
+// plane in one block, A to A; the plane's B fields never exist.  A pair of real fields at a time is
+// transformed along y in LDS (2 KX columns of N points), read back as N lines h = f + i g and
+// transformed along x, each line by the TX lanes of a wavefront that hold it; the products stay in
+// registers, N E points of them per lane, and go back the same way.  A grid of this size is bound by
+// launches and by the chain of dependent steps inside a block, and a batch of them by the fields of B
+// (6 + 3S and 3 + S for S scalars) that the three passes write and read back.
+// (16 x 64^3 FP32, two scalars: 90 us against 151 in three passes; one 32^3 FP64 plane set, one
+// scalar: 14 us against 30.)  Larger planes do not fit: N^2 points are N^2 / 8 lanes of eight points, and each lane holds
+// eight values per point.
+// A block reads every A field of its plane before it writes over it: outputs go to fields 0 .. 2
+// after the velocity's inputs, and a_s to 3 + s, which lies below the inputs 5 + 2s, 6 + 2s of every
+// scalar still to come.
+// With fsin the first block of a slot computes the forcing amplitude, as in the y inverse.
+// ---------------------------------------------------------------------------
+template <int N>
+constexpr bool has_plane() {
+  return N == 32 || N == 64;
+}
+template <int N, typename T>
+struct PlaneCfg {
+  static constexpr int E = N <= 32 ? 4 : 8;  // elements per thread, columns and lines
+  static constexpr int TT = N / E;           // threads per column, lanes per line
+  static constexpr int THREADS = N * TT;
+  static constexpr int K = (N - 1) / 3, M = 2 * K + 1, KX = K + 1;
+  static constexpr int NC = 2 * KX;  // columns of a pair
+  static constexpr int ITEMS = NC * TT;
+  static constexpr int LP = LinePad<N>::value;
+  // waves per SIMD for the register allocator: at four, two FP32 blocks of 64^3 share a CU but
+  // spill 58 registers (16 x 64^3, two scalars: 138 us against 90)
+  static constexpr int WAVES = 2;
+  static_assert(ITEMS <= THREADS && 2 * ITEMS >= THREADS, "a pair's columns must cover over half the block");
+};
+
+template <int N, typename T>
+__global__ void __launch_bounds__((PlaneCfg<N, T>::THREADS), (PlaneCfg<N, T>::WAVES))
+k_plane(cpx<T>* __restrict__ abuf, const cpx<T>* __restrict__ tw_g, const SlotDev* __restrict__ slots,
+        DynDev* __restrict__ dyn, Geom g, const cpx<T>* __restrict__ fsin, int want_max) {
+  using C = PlaneCfg<N, T>;
+  constexpr int E = C::E, TT = C::TT, K = C::K, M = C::M, KX = C::KX, NC = C::NC;
+  constexpr int NQ = (K + TT) / TT;  // half-spectrum entries per lane
+  __shared__ cpx<T> pl[N * NC];      // the pair's plane: row y, columns (field, kx)
+  __shared__ cpx<T> ll[N * C::LP];   // line exchange
+  __shared__ cpx<T> stw[N];
+  const int slot = blockIdx.y;
+  const SlotDev& sp = slots[slot];
+  if (!sp.active) return;
+  if (blockIdx.x == 0) {
+    forcing_block(fsin, sp, dyn[slot], g, slot, reinterpret_cast<double*>(ll));
+    return;
+  }
+  const int z = blockIdx.x - 1;
+  stage_twiddles<N>(stw, tw_g);
+  // column role: the threads past the pair's columns repeat the first ones' work and store nothing
+  const bool own = (int)threadIdx.x < C::ITEMS;
+  const int item = own ? threadIdx.x : threadIdx.x - C::ITEMS;
+  const int kx = item % KX, fld = (item / KX) & 1, jc = item / NC;
+  const int col = fld * KX + kx;
+  const LdsCol<T, NC> clds{pl + col};
+  // line role
+  const int y = threadIdx.x / TT, jl = threadIdx.x % TT;
+  const LdsLine<T, N, E> llds{ll + y * C::LP};
+  const cpx<T>* prow = pl + y * NC;
+  cpx<T>* aplane = abuf + (long long)slot * g.FA * g.a_field + a_row(z, 0, M, g.PX) + kx;
+
+  // v += sg (1, i kx or i ky by type) times A field f of the thread's column
+  cpx<T> v[E];
+  auto term = [&](int f, int type, T sg) __attribute__((always_inline)) {
+    const cpx<T>* p = aplane + (long long)f * g.a_field;
+    cpx<T> x[E];
+    // every load in flight before the first is used: rows past the retained ones read row 0
+    static_for<0, E>([&](auto mc) {
+      constexpr int m = decltype(mc)::value;
+      if constexpr (!ColPos<N, TT, K>::cut(m)) {
+        const int kc = compact_of(jc + TT * m, N, K, M);
+        x[m] = p[(kc < 0 ? 0 : kc) * g.PX];
+      }
+    });
+    static_for<0, E>([&](auto mc) {
+      constexpr int m = decltype(mc)::value;
+      if constexpr (!ColPos<N, TT, K>::cut(m)) {
+        const int n = jc + TT * m;
+        const T fac = type == 0 ? sg : sg * T(type == 1 ? kx : wave_of(n, N));
+        const cpx<T> w = type == 0 ? x[m] : mul_i(x[m]);
+        if (compact_of(n, N, K, M) >= 0) v[m] = v[m] + fac * w;
+      }
+    });
+  };
+  auto clear = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int m = 0; m < E; ++m) v[m] = czero<T>();
+  };
+  // inverse of the pair whose columns are in v: physical values of both fields at x = jl + TT m
+  auto inverse = [&](cpx<T> (&h)[E]) __attribute__((always_inline)) {
+    fft<N, E, true>(v, clds, jc, stw);
+#pragma unroll
+    for (int m = 0; m < E; ++m) clds.st(jc + TT * m, v[m], 0);
+    __syncthreads();
+    static_for<0, E>([&](auto mc) {
+      constexpr int m = decltype(mc)::value;
+      h[m] = czero<T>();
+      if constexpr (!ColPos<N, TT, K>::cut(m)) {
+        const int n = jl + TT * m;
+        const bool neg = TT * m > K;  // the positions of one m lie on one side of the cut
+        const int k = neg ? N - n : n, kr = k <= K ? k : 0;
+        cpx<T> a = prow[kr], b = prow[KX + kr];
+        if (k == 0) a.y = b.y = T(0);  // a complex-to-real transform keeps the real part
+        if (neg) {
+          a = conj(a);
+          b = conj(b);
+        }
+        if (k <= K) h[m] = a + mul_i(b);
+      }
+    });
+    __syncthreads();  // the plane may be written again
+    fft<N, E, true, WaveSync>(h, llds, jl, stw);
+  };
+  // forward of the real pair (p, q) into A fields fp and fq (fq < 0: p alone)
+  auto forward = [&](const T (&p)[E], const T (&q)[E], int fp, int fq) __attribute__((always_inline)) {
+    cpx<T> h[E];
+#pragma unroll
+    for (int m = 0; m < E; ++m) h[m] = {p[m], q[m]};
+    fft<N, E, false, WaveSync>(h, llds, jl, stw);
+#pragma unroll
+    for (int m = 0; m < E; ++m) llds.st(jl + TT * m, h[m]);
+    WaveSync::sync();
+    cpx<T>* row = pl + y * NC;
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) {
+      const int k = jl + TT * i;
+      if (k <= K) {
+        const cpx<T> zk = llds.ld(k), zc = conj(llds.ld((N - k) & (N - 1)));
+        row[k] = T(0.5) * (zk + zc);
+        row[KX + k] = mul_mi(T(0.5) * (zk - zc));
+      }
+    }
+    WaveSync::sync();
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < E; ++m) v[m] = clds.ld(jc + TT * m, 0);
+    __syncthreads();
+    fft<N, E, false>(v, clds, jc, stw);
+    const int f = fld == 0 ? fp : fq;
+    if (!own || f < 0) return;
+    cpx<T>* o = aplane + (long long)f * g.a_field;
+    static_for<0, E>([&](auto mc) {
+      constexpr int m = decltype(mc)::value;
+      const int kc = compact_of(jc + TT * m, N, K, M);
+      if (kc >= 0) o[kc * g.PX] = v[m];
+    });
+  };
+
+  cpx<T> h[E];
+  T u1[E], u2[E], u3[E], c1[E], c2[E], c3[E];
+  // omega2 = dz u1 - dx u3, omega3 = dx u2 - dy u1
+  clear();
+  term(fld ? 1 : 3, fld ? 1 : 0, T(1));
+  term(fld ? 0 : 2, fld ? 2 : 1, T(-1));
+  inverse(h);
+#pragma unroll
+  for (int m = 0; m < E; ++m) {
+    c2[m] = h[m].x;  // omega2 and omega3, until the products take their place
+    c3[m] = h[m].y;
+  }
+  // u3 and omega1 = dy u3 - dz u2
+  clear();
+  term(2, fld ? 2 : 0, T(1));
+  if (fld) term(4, 0, T(-1));
+  inverse(h);
+#pragma unroll
+  for (int m = 0; m < E; ++m) {
+    u3[m] = h[m].x;
+    c1[m] = h[m].y;
+  }
+  clear();
+  term(fld, 0, T(1));
+  inverse(h);
+  T mx = T(0);
+#pragma unroll
+  for (int m = 0; m < E; ++m) {
+    u1[m] = h[m].x;
+    u2[m] = h[m].y;
+    const T w1 = c1[m], w2 = c2[m], w3 = c3[m];
+    c1[m] = u2[m] * w3 - u3[m] * w2;
+    c2[m] = u3[m] * w1 - u1[m] * w3;
+    c3[m] = u1[m] * w2 - u2[m] * w1;
+    const T sm = fabs(u1[m]) + fabs(u2[m]) + fabs(u3[m]);
+    mx = (sm > mx || sm != sm) ? sm : mx;  // keeps NaN
+  }
+  if (want_max) {
+    double mm = (double)mx;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      const double b = __shfl_xor(mm, o);
+      mm = (b > mm || b != b) ? b : mm;
+    }
+    if (threadIdx.x % 64 == 0) atomicMax(&dyn[slot].umax, (unsigned long long)__double_as_longlong(mm));
+  }
+  T zero[E];
+#pragma unroll
+  for (int m = 0; m < E; ++m) zero[m] = T(0);
+  forward(c1, c2, 0, 1);
+  const int S = g.S;
+  if (S == 0) forward(c3, zero, 2, -1);
+  // a_s = u.grad phi_s + g_s.u, the scalars in pairs; c3 travels with the first
+  T as0[E], as1[E];
+  auto products = [&](int s, T (&as)[E]) __attribute__((always_inline)) {
+    clear();
+    term(5 + 2 * s, fld ? 2 : 1, T(1));
+    inverse(h);
+    const T g0 = T(sp.g[s][0]), g1 = T(sp.g[s][1]), g2 = T(sp.g[s][2]);
+#pragma unroll
+    for (int m = 0; m < E; ++m)
+      as[m] = u1[m] * h[m].x + u2[m] * h[m].y + (g0 * u1[m] + g1 * u2[m] + g2 * u3[m]);
+  };
+  for (int s = 0; s < S; s += 2) {
+    const bool two = s + 1 < S;
+    products(s, as0);
+    if (two) products(s + 1, as1);
+    // both z derivatives share one transform
+    clear();
+    if (fld == 0 || two) term(6 + 2 * (s + fld), 0, T(1));
+    inverse(h);
+#pragma unroll
+    for (int m = 0; m < E; ++m) {
+      as0[m] += u3[m] * h[m].x;
+      as1[m] = two ? as1[m] + u3[m] * h[m].y : T(0);
+    }
+    forward(c3, as0, s == 0 ? 2 : 2 + s, 3 + s);
+    if (two) {
+      if (s == 0 && S > 2) {
+#pragma unroll
+        for (int m = 0; m < E; ++m) c3[m] = as1[m];  // a_1 waits for a_2
+      } else {
+        forward(as1, zero, 4 + s, -1);
+      }
+    }
   }
 }
 
@@ -2583,11 +2823,29 @@ struct Stage {
     if (flags & kStageZinv)
       with_sched<N>(x.psched[kPassZInverse], [&](auto v) { Step<N, T, decltype(v)::value>::z_inverse(x, sin, s); });
     if (flags & kStagePrologue) return;
-    with_sched<N>(x.psched[kPassYInverse], [&](auto v) { Step<N, T, decltype(v)::value>::y_inverse(x, sin, s); });
-    with_sched<N>(x.psched[kPassX],
-                  [&](auto v) { Step<N, T, decltype(v)::value>::x_pass(x, g, want_max ? kXMax : 0, s); });
-    with_sched<N>(x.psched[kPassYForward],
-                  [&](auto v) { Step<N, T, decltype(v)::value>::y_forward(x, stage == 0, dt_arg, s); });
+    bool plane = false;
+    if constexpr (has_plane<N>()) {
+      // schedule 0 of the three passes is the plane pass, where there is one
+      plane = x.psched[kPassYInverse] == 0 && x.psched[kPassX] == 0 && x.psched[kPassYForward] == 0;
+      if (plane) {
+        {
+          TimedLaunch tl(x.timer, KID_XPASS, s);
+          k_plane<N, T><<<dim3(N + 1, g.batch), PlaneCfg<N, T>::THREADS, 0, s>>>(
+              static_cast<cpx<T>*>(x.abuf), static_cast<const cpx<T>*>(x.tw), x.slots, x.dyn, g, sin, want_max);
+        }
+        if (stage == 0) {
+          TimedLaunch tl(x.timer, KID_DT, s);
+          k_step_dt<<<g.batch, 64, 0, s>>>(x.slots, x.dyn, g, dt_arg);
+        }
+      }
+    }
+    if (!plane) {
+      with_sched<N>(x.psched[kPassYInverse], [&](auto v) { Step<N, T, decltype(v)::value>::y_inverse(x, sin, s); });
+      with_sched<N>(x.psched[kPassX],
+                    [&](auto v) { Step<N, T, decltype(v)::value>::x_pass(x, g, want_max ? kXMax : 0, s); });
+      with_sched<N>(x.psched[kPassYForward],
+                    [&](auto v) { Step<N, T, decltype(v)::value>::y_forward(x, stage == 0, dt_arg, s); });
+    }
     if (stage == 0 && x.stochastic) {
       // returns at once for slots without the stochastic forcing
       TimedLaunch tl(x.timer, KID_DT, s);
@@ -2829,6 +3087,7 @@ struct Engine {
     add_scheds<0, sched_count<N>()>(o);
     o.rhs_mixed = &Stage<N, T>::rhs_stage;
     o.rhs_phase = &Stage<N, T>::rhs_phase;
+    o.plane = has_plane<N>();
     o.init_field = &init_field;
     o.get_state = &get_state;
     o.set_state = &set_state;
