@@ -21,7 +21,7 @@ Ops ops_n256(int);
 Ops ops_n512(int);
 Ops ops_n1024(int);
 Ops ops_general(int);
-int general_x_lines(int n, int precision);
+int general_x_lines(int n, int precision, int batch);
 }  // namespace psdns
 
 using namespace psdns;
@@ -545,7 +545,7 @@ psdns_status psdns_plan_create(const psdns_plan_params* p, psdns_plan** out) {
   plan->p = *p;
   plan->ops = ops_for(p);
   plan->general = general_plan(p);
-  if (plan->general) plan->ops.sched[0].x_lines = general_x_lines(p->n, p->precision);
+  if (plan->general) plan->ops.sched[0].x_lines = general_x_lines(p->n, p->precision, p->batch);
   plan->L = make_layout(p);
   hipError_t e = hipGetDevice(&plan->device);
   if (e != hipSuccess) {
@@ -693,7 +693,7 @@ psdns_status psdns_use_general_kernels(psdns_plan* plan) {
     plan->graph_exec = nullptr;
   }
   plan->ops = ops_general(plan->p.precision);
-  plan->ops.sched[0].x_lines = general_x_lines(plan->p.n, plan->p.precision);
+  plan->ops.sched[0].x_lines = general_x_lines(plan->p.n, plan->p.precision, plan->p.batch);
   for (int p = 0; p < kNumPasses; ++p) plan->psched[p] = 0;
   plan->general = true;
   return PSDNS_OK;

@@ -346,39 +346,48 @@ inline Shape col_shape(int N, int csize) {
 }
 
 // Launch shape of the step's column passes: W columns, TT threads per column, the root table and
-// two line buffers in LDS.  A stage of radix R takes ceil((N/R) / TT) butterflies per thread, so
-// a TT that does not divide well leaves lanes idle in every stage (N = 520 with 64 threads per
-// column: 65 radix-8 butterflies in two turns).  TT is the multiple of a wavefront, between half
-// and all of the block's thread limit, that wastes least: the smallest TT times the sum over the
-// stages of turns times the cost of a butterfly (about its instructions), the larger on a tie.
+// two line buffers in LDS.  A stage of radix R takes ceil((N/R) / TT) turns, each the time of a
+// butterfly (radix_cost, about its instructions); as many blocks as LDS and the registers'
+// wavefronts allow share a CU and fill each other's barriers, and the grid goes over the 256 CUs in
+// rounds of them.  TT is the whole number of wavefronts with the least sum of turns times rounds,
+// the smaller block on a tie
+// (200^3 FP64 y inverse: 40 threads per column, one turn in every stage but one block per CU,
+// 0.50 ms; 32 threads, two turns and two blocks, 0.39.  300^3 FP32: 64 threads 0.55, 32 0.47).
 template <typename T>
 constexpr int col_threads() {
   return sizeof(T) == 4 ? 1024 : 512;  // FP64 butterflies of radix 11 and 13 need 256 registers
 }
 inline int radix_cost(int R) { return R % 2 ? R * (R + 6) : 10 * R; }
-inline Shape step_shape(const Factors& f, int csize, int maxt) {
-  Shape s{};
+// maxt: threads per block; waves: wavefronts per CU the registers allow; kxs columns in each of
+// rows rows; maxpos: positions of a column that a thread can hold (the z forward)
+inline Shape step_shape(const Factors& f, int csize, int maxt, int waves, int kxs, long long rows,
+                        int maxpos = 1 << 20) {
   const int N = f.n;
-  auto lds = [&](int W) { return ((size_t)root_table_entries(N) + 2 * (size_t)W * N) * csize; };
-  s.W = csize == 8 ? 16 : 8;
-  while (s.W > 1 && lds(s.W) > 160 * 1024) s.W /= 2;
-  const int unit = s.W < 64 ? 64 / s.W : 1;
-  long long best = -1;
-  for (int t = maxt / s.W / unit * unit; t >= unit && 2 * t * s.W >= maxt; t -= unit) {
-    long long cost = 0;
-    for (int i = 0; i < f.nst; ++i) cost += (long long)((N / f.r[i] + t - 1) / t) * radix_cost(f.r[i]);
-    cost *= t;
-    if (best < 0 || cost < best) {
-      best = cost;
-      s.TT = t;
+  Shape best{};
+  for (int W = csize == 8 ? 16 : 8; W >= 1; W /= 2) {
+    const size_t lds = ((size_t)root_table_entries(N) + 2 * (size_t)W * N) * csize;
+    if (lds > 160 * 1024) continue;
+    const int unit = 64 / W;
+    double least = 0.0;
+    for (int t = unit; t * W <= maxt; t += unit) {
+      if (t * maxpos < N && t * W + unit * W <= maxt) continue;
+      double turns = 0.0;
+      for (int i = 0; i < f.nst; ++i) turns += (double)((N / f.r[i] + t - 1) / t) * radix_cost(f.r[i]);
+      const int byw = waves / (t * W / 64), byl = (int)(160 * 1024 / lds);
+      const int blocks = byw < 1 ? 1 : byw < byl ? byw : byl;
+      const long long grid = (kxs + W - 1) / W * rows;
+      const double cost = turns * (double)((grid + 256 * blocks - 1) / (256 * blocks));
+      if (best.TT == 0 || cost < least) {
+        least = cost;
+        best.W = W;
+        best.TT = t;
+        best.lds = lds;
+      }
     }
+    if (best.TT * maxpos >= N) return best;
+    best.TT = 0;  // the line is too long for W columns: narrower blocks
   }
-  // small lines: no more threads than the widest stage has butterflies
-  int nb = 0;
-  for (int i = 0; i < f.nst; ++i) nb = nb > N / f.r[i] ? nb : N / f.r[i];
-  if (s.TT > nb) s.TT = (nb + unit - 1) / unit * unit;
-  s.lds = lds(s.W);
-  return s;
+  return best;
 }
 
 // root table into LDS; the line buffers follow it
@@ -612,7 +621,7 @@ k_y_inverse(const cpx<T>* __restrict__ abuf, cpx<T>* __restrict__ bbuf, const cp
 }
 
 // ---------------------------------------------------------------------------
-// x pass: one wavefront per (z, y) line, lw lines per block.  Pairs of real fields travel as
+// x pass: TL lanes of one wavefront per (z, y) line, lw lines per block.  Pairs of real fields travel as
 // one complex line h = f + i g (half-spectrum entries kx <= K, their conjugates at N - kx);
 // the products u x omega and u.grad phi_s + g_s.u are formed pointwise and transformed back,
 // kx <= K written in place into the first F fields of B.  shift multiplies the inputs by
@@ -620,26 +629,53 @@ k_y_inverse(const cpx<T>* __restrict__ abuf, cpx<T>* __restrict__ bbuf, const cp
 // max |u1|+|u2|+|u3| joins the slot's maximum (Eq. (10)).
 //
 // The block copies the root table (stage twiddles, odd-radix roots, half-cell shifts) to
-// LDS once for its lines; each wave then owns two line buffers and synchronises its
-// transform stages alone.  Lane j keeps positions n = j + 64 q (q < P) of the physical
+// LDS once for its lines; each line then owns two line buffers and its wave synchronises the
+// transform stages alone.  Lane j keeps positions n = j + TL q (q < P) of the physical
 // fields in registers: u1 u2 u3, and c1 c2 c3 while they are formed; c1 and c2 are
 // transformed as soon as they exist, and each scalar product then pairs with the field
 // before it, so that at most six fields are live.
 // ---------------------------------------------------------------------------
-constexpr int kXMaxLines = 4;     // lines (wavefronts) per block
-
-// positions per lane of the physical fields of an N-point line; the half spectrum
-// kx <= K <= N/2 then needs at most P/2 + 1 entries per lane
-inline int x_positions(int N) { return (N + 63) / 64; }
+constexpr int kXThreads = 256;
 constexpr int kMaxPositions = 16;  // N <= 1024: 64 lanes per x line, 64 or more threads per z column
-// lines per block: as many as fit two blocks in the 160 KB of a CU
-inline int x_lines(int N, int csize) {
-  int lw = kXMaxLines;
-  while (lw > 1 && ((size_t)root_table_entries(N) + (size_t)lw * 2 * N) * csize > 80 * 1024) lw /= 2;
-  return lw;
-}
+
+// Launch shape of the x pass: TL lanes per line (16, 32 or 64: a line stays inside a wavefront), lw
+// lines per block, P positions per lane.  A stage of radix R keeps N/R lanes of a line busy, a
+// fraction of 64 where N is small (N = 104: 8 and 13), so short lines share a wavefront: TL is the
+// one with the least sum of turns (as in step_shape) times rounds of wavefronts over the chip (12
+// per CU), with at most nine positions per lane in FP32 and eight in FP64 below 64 lanes, which is
+// what six fields leave of the registers; seven and eight FP64 positions spill, for about a third of
+// the time (200^3: 32 lanes of seven 1.50 ms a right-hand side, 64 lanes of four 1.34; 104^3 in a
+// batch of 14, 16 lanes of seven against 64 of two: 11.7 ms a step against 13.8, FP32 5.6 against
+// 7.1).  Blocks hold as many lines as leave two of them in the 160 KB of a CU.
+struct XShape {
+  int TL, lw, P;
+  size_t lds;
+};
 inline size_t x_lds_bytes(int N, int csize, int lw) {
   return ((size_t)root_table_entries(N) + (size_t)lw * 2 * N) * csize;
+}
+inline XShape x_shape(const Factors& f, int csize, long long lines) {
+  const int N = f.n;
+  XShape best{};
+  double least = 0.0;
+  for (int TL = 64; TL >= 16; TL /= 2) {
+    const int P = (N + TL - 1) / TL;
+    if (TL < 64 && P > (csize == 8 ? 9 : 8)) break;
+    double turns = 0.0;
+    for (int i = 0; i < f.nst; ++i) turns += (double)((N / f.r[i] + TL - 1) / TL) * radix_cost(f.r[i]);
+    const long long waves = (lines * TL + 63) / 64;
+    const double cost = turns * (double)((waves + 3071) / 3072) * (csize == 16 && P >= 7 ? 1.3 : 1.0);
+    if (best.TL == 0 || cost < least) {
+      least = cost;
+      best.TL = TL;
+      best.P = P;
+    }
+  }
+  best.lw = kXThreads / best.TL;
+  // whole wavefronts of lines
+  while (best.lw * best.TL > 64 && x_lds_bytes(N, csize, best.lw) > 80 * 1024) best.lw /= 2;
+  best.lds = x_lds_bytes(N, csize, best.lw);
+  return best;
 }
 
 // waves per SIMD the register allocation of the x pass aims at (six fields of P positions
@@ -650,9 +686,9 @@ constexpr int x_waves() {
 }
 
 template <typename T, int P>
-__global__ void __launch_bounds__(64 * kXMaxLines, (x_waves<T, P>()))
+__global__ void __launch_bounds__(kXThreads, (x_waves<T, P>()))
 k_x_pass(cpx<T>* __restrict__ bbuf, const cpx<T>* __restrict__ tw_g, const SlotDev* __restrict__ slots,
-         DynDev* __restrict__ dyn, Geom g, Factors fx, int shift, int umax) {
+         DynDev* __restrict__ dyn, Geom g, Factors fx, int TL, int shift, int umax) {
   extern __shared__ char lds_raw[];
   const int N = g.N, S = g.S, K = g.K;
   const int nt = (int)root_table_entries(N);
@@ -662,10 +698,12 @@ k_x_pass(cpx<T>* __restrict__ bbuf, const cpx<T>* __restrict__ tw_g, const SlotD
   if (!sp.active) return;
   for (int i = threadIdx.x; i < nt; i += blockDim.x) tw[i] = tw_g[i];
   __syncthreads();
-  const int lw = blockDim.x / 64, wv = threadIdx.x / 64, j = threadIdx.x % 64;
-  const long long line = (long long)blockIdx.x * lw + wv;  // z * N + y
-  if (line >= (long long)N * N) return;
-  cpx<T>* b0 = tw + nt + (size_t)wv * 2 * N;
+  const int lw = blockDim.x / TL, li = threadIdx.x / TL, j = threadIdx.x % TL;
+  // z * N + y; lanes past the last line repeat it and store nothing
+  const long long line0 = (long long)blockIdx.x * lw + li, lines = (long long)N * N;
+  const bool own = line0 < lines;
+  const long long line = own ? line0 : lines - 1;
+  cpx<T>* b0 = tw + nt + (size_t)li * 2 * N;
   cpx<T>* b1 = b0 + N;
   cpx<T>* lbase = bbuf + (long long)slot * g.FB * g.b_field + line * g.PX;
   // entry kx of the combination (field f, optional i kx factor, sign)
@@ -703,7 +741,7 @@ k_x_pass(cpx<T>* __restrict__ bbuf, const cpx<T>* __restrict__ tw_g, const SlotD
   //   5  inverse dz phi_s, then a_s += u3 dz phi_s
   // c1 and c2 are transformed first; c3 then waits in A for a_0, and every second scalar
   // product waits in A for the next.  For an inverse job a lane reads its half-spectrum entries
-  // k = j + 64 q once, all of them before any is used, and writes position k and its conjugate
+  // k = j + TL q once, all of them before any is used, and writes position k and its conjugate
   // mirror N - k of the line.
   constexpr int Q = P / 2 + 1;
   T u1[P], u2[P], u3[P], A[P], B[P], C[P];
@@ -713,7 +751,7 @@ k_x_pass(cpx<T>* __restrict__ bbuf, const cpx<T>* __restrict__ tw_g, const SlotD
     if (job == 3) {
 #pragma unroll
       for (int i = 0; i < P; ++i) {
-        const int n = j + 64 * i;
+        const int n = j + TL * i;
         if (n < N) b0[n] = {A[i], fb >= 0 ? B[i] : T(0)};
       }
     } else {
@@ -730,14 +768,14 @@ k_x_pass(cpx<T>* __restrict__ bbuf, const cpx<T>* __restrict__ tw_g, const SlotD
       cpx<T> va[Q], vb[Q];
 #pragma unroll
       for (int q = 0; q < Q; ++q) {
-        const int k = j + 64 * q;
+        const int k = j + TL * q;
         va[q] = k <= K ? coeff(qa, k) : cpx<T>{T(0), T(0)};
         vb[q] = k <= K ? coeff(qb, k) : cpx<T>{T(0), T(0)};
       }
-      for (int n = K + 1 + j; n < N - K; n += 64) b0[n] = {T(0), T(0)};
+      for (int n = K + 1 + j; n < N - K; n += TL) b0[n] = {T(0), T(0)};
 #pragma unroll
       for (int q = 0; q < Q; ++q) {
-        const int k = j + 64 * q;
+        const int k = j + TL * q;
         if (k <= K) {
           b0[k] = conj(va[q] + mul_i(vb[q]));
           if (k > 0) b0[N - k] = conj(conj(va[q]) + mul_i(conj(vb[q])));
@@ -745,9 +783,9 @@ k_x_pass(cpx<T>* __restrict__ bbuf, const cpx<T>* __restrict__ tw_g, const SlotD
       }
     }
     WaveSync::sync();
-    const cpx<T>* r = fft_in<false, WaveSync, T>([&](int n) { return b0[n]; }, b1, b0, fx, 1, 0, j, 64, tw);
+    const cpx<T>* r = fft_in<false, WaveSync, T>([&](int n) { return b0[n]; }, b1, b0, fx, 1, 0, j, TL, tw);
     if (job == 3) {
-      for (int k = j; k <= K; k += 64) {
+      for (int k = j; k <= K; k += TL) {
         const cpx<T> zk = r[k], zc = conj(r[(N - k) % N]);
         cpx<T> Pv = T(0.5) * (zk + zc);
         cpx<T> Qv = mul_mi(T(0.5) * (zk - zc));
@@ -756,6 +794,7 @@ k_x_pass(cpx<T>* __restrict__ bbuf, const cpx<T>* __restrict__ tw_g, const SlotD
           Pv = cmul(Pv, e);
           Qv = cmul(Qv, e);
         }
+        if (!own) continue;
         lbase[(long long)fa * g.b_field + k] = Pv;
         if (fb >= 0) lbase[(long long)fb * g.b_field + k] = Qv;
       }
@@ -764,7 +803,7 @@ k_x_pass(cpx<T>* __restrict__ bbuf, const cpx<T>* __restrict__ tw_g, const SlotD
       T rx[P], ry[P];
 #pragma unroll
       for (int i = 0; i < P; ++i) {
-        const int n = j + 64 * i;
+        const int n = j + TL * i;
         rx[i] = n < N ? r[n].x : T(0);
         ry[i] = n < N ? -r[n].y : T(0);
       }
@@ -855,12 +894,13 @@ k_x_pass(cpx<T>* __restrict__ bbuf, const cpx<T>* __restrict__ tw_g, const SlotD
     }
   }
   if (umax) {
+    if (!own) mx = 0.0;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
       const double b = __shfl_xor(mx, o);
       mx = (b > mx || b != b) ? b : mx;
     }
-    if (j == 0) atomicMax(&dyn[slot].umax, (unsigned long long)__double_as_longlong(mx));
+    if (threadIdx.x % 64 == 0) atomicMax(&dyn[slot].umax, (unsigned long long)__double_as_longlong(mx));
   }
 }
 
@@ -929,18 +969,14 @@ __device__ __forceinline__ cpx<T> update(const GStage<T>& a, long long o, cpx<T>
   return nxt;
 }
 
-// Launch shape of the z-forward pass: blocks of at most 512 threads (64 columns of threads in
-// FP32, 128 in FP64, and 8 or 4 columns), so that a thread may hold its P positions
-// n = j + TT m of three fields (c1, c2 and the current one) in registers.
-inline Shape zf_shape(int N, int csize) {
-  Shape s{};
-  s.TT = csize == 8 ? 64 : 128;
-  if (s.TT > N / 2) s.TT = N / 2;
-  auto lds = [&](int W) { return ((size_t)root_table_entries(N) + 2 * (size_t)W * N) * csize; };
-  s.W = csize == 8 ? 8 : 4;
-  while (s.W > 1 && lds(s.W) > 160 * 1024) s.W /= 2;
-  s.lds = lds(s.W);
-  return s;
+// Launch shape of the z-forward pass: a thread holds its positions n = j + TT m, m < P, of three
+// fields (c1, c2 and the current one) in registers beside its butterflies, so P stays at nine in
+// FP32 and five in FP64 where blocks of at most 512 threads (256 registers) allow it: 13 positions
+// on 128-byte rows spill (520^3 FP32: 2.19 ms; nine on 64-byte rows 1.62).
+template <typename T>
+inline Shape zf_shape(const Factors& f, const Geom& g) {
+  const int least = sizeof(T) == 4 ? (f.n + 63) / 64 : (f.n + 127) / 128, fine = sizeof(T) == 4 ? 9 : 5;
+  return step_shape(f, (int)(2 * sizeof(T)), 512, 8, g.KX, (long long)g.M * g.batch, least > fine ? least : fine);
 }
 inline int zf_positions(int N, int TT) { return (N + TT - 1) / TT; }
 

@@ -2,6 +2,7 @@
 // statistics and the state conversions of plans whose N is not a power of two or that use
 // the paper's phase-shift dealiasing.  N, K and the retained set come from the plan's
 // geometry at run time; one schedule.
+#pragma once
 #include <type_traits>
 
 #include "engine.hpp"
@@ -53,16 +54,13 @@ void with_positions(int p, Fn&& fn) {
 template <typename T>
 struct GEngine {
   static Shape shape(const Geom& g) { return gen::col_shape(g.N, (int)sizeof(cpx<T>)); }
-  // x pass: P positions per lane of the physical fields, lw lines (wavefronts) per block
+  // x pass: P positions per lane of the physical fields
   template <int P>
-  static void launch_x(const Ctx& x, int shift, int umax, hipStream_t s) {
+  static void launch_x(const Ctx& x, const gen::XShape& sh, const Factors& f, int shift, int umax, hipStream_t s) {
     const Geom& g = x.g;
-    const int csize = (int)sizeof(cpx<T>);
-    const int lw = gen::x_lines(g.N, csize);
     const long long lines = (long long)g.N * g.N;
-    gen::k_x_pass<T, P><<<dim3((unsigned)((lines + lw - 1) / lw), g.batch), 64 * lw, gen::x_lds_bytes(g.N, csize, lw),
-                          s>>>(static_cast<cpx<T>*>(x.bbuf), static_cast<const cpx<T>*>(x.tw), x.slots, x.dyn, g,
-                               gen::step_factors(g.N), shift, umax);
+    gen::k_x_pass<T, P><<<dim3((unsigned)((lines + sh.lw - 1) / sh.lw), g.batch), sh.TL * sh.lw, sh.lds, s>>>(
+        static_cast<cpx<T>*>(x.bbuf), static_cast<const cpx<T>*>(x.tw), x.slots, x.dyn, g, f, sh.TL, shift, umax);
   }
   // the line-moment kernel of the statistics: up to 256 threads per line
   static int moment_threads(const Geom& g) {
@@ -88,16 +86,19 @@ struct GEngine {
         g, gen::factor(g.N), sp, sh.W, sh.TT, shift);
   }
   static void x_pass(const Ctx& x, int shift, int umax, hipStream_t s) {
-    with_positions(gen::x_positions(x.g.N), [&](auto p) { launch_x<decltype(p)::value>(x, shift, umax, s); });
+    const Factors f = gen::step_factors(x.g.N);
+    const gen::XShape sh = gen::x_shape(f, (int)sizeof(cpx<T>), (long long)x.g.N * x.g.N * x.g.batch);
+    with_positions(sh.P, [&](auto p) { launch_x<decltype(p)::value>(x, sh, f, shift, umax, s); });
   }
   // the column passes of the step
-  static Shape step_shape(const Factors& f) {
-    return gen::step_shape(f, (int)sizeof(cpx<T>), gen::col_threads<T>());
+  static Shape step_shape(const Factors& f, const Geom& g, int rows) {
+    return gen::step_shape(f, (int)sizeof(cpx<T>), gen::col_threads<T>(), sizeof(T) == 4 ? 16 : 8, g.KX,
+                           (long long)rows * g.batch);
   }
   static void z_inverse_step(const Ctx& x, const void* in, int shift, hipStream_t s) {
     const Geom& g = x.g;
     const Factors f = gen::step_factors(g.N);
-    const Shape sh = step_shape(f);
+    const Shape sh = step_shape(f, g, g.M);
     const T scale = T(1) / (T(g.N) * T(g.N) * T(g.N));
     gen::k_z_inverse_step<T><<<dim3((g.KX + sh.W - 1) / sh.W, g.M, g.batch), sh.W * sh.TT, sh.lds, s>>>(
         static_cast<const cpx<T>*>(in), static_cast<cpx<T>*>(x.abuf), static_cast<const cpx<T>*>(x.tw), x.slots, g, f,
@@ -106,7 +107,7 @@ struct GEngine {
   static void y_inverse_step(const Ctx& x, int shift, hipStream_t s) {
     const Geom& g = x.g;
     const Factors f = gen::step_factors(g.N);
-    const Shape sh = step_shape(f);
+    const Shape sh = step_shape(f, g, g.N);
     gen::k_y_inverse_step<T><<<dim3((g.KX + sh.W - 1) / sh.W, g.N, g.batch), sh.W * sh.TT, sh.lds, s>>>(
         static_cast<const cpx<T>*>(x.abuf), static_cast<cpx<T>*>(x.bbuf), static_cast<const cpx<T>*>(x.tw), x.slots,
         g, f, sh.W, sh.TT, shift);
@@ -114,7 +115,7 @@ struct GEngine {
   static void y_forward_step(const Ctx& x, void* out, int out_fields, int shift, hipStream_t s) {
     const Geom& g = x.g;
     const Factors f = gen::step_factors(g.N);
-    const Shape sh = step_shape(f);
+    const Shape sh = step_shape(f, g, g.N);
     gen::k_y_forward_step<T><<<dim3((g.KX + sh.W - 1) / sh.W, g.N, g.batch), sh.W * sh.TT, sh.lds, s>>>(
         static_cast<const cpx<T>*>(x.bbuf), static_cast<cpx<T>*>(out), out_fields, static_cast<const cpx<T>*>(x.tw),
         x.slots, g, f, g.F, sh.W, sh.TT, shift);
@@ -168,14 +169,14 @@ struct GEngine {
     sa.fband = x.fband;
     sa.stage = stage;
     TimedLaunch tl(x.timer, KID_ZFWD, s);
-    with_positions(gen::zf_positions(g.N, gen::zf_shape(g.N, (int)sizeof(cpx<T>)).TT),
+    with_positions(gen::zf_positions(g.N, gen::zf_shape<T>(gen::step_factors(g.N), g).TT),
                    [&](auto p) { launch_zf<decltype(p)::value>(x, sa, s); });
   }
   // z forward + update: P positions per thread of each column
   template <int P>
   static void launch_zf(const Ctx& x, const gen::GStage<T>& sa, hipStream_t s) {
     const Geom& g = x.g;
-    const Shape sh = gen::zf_shape(g.N, (int)sizeof(cpx<T>));
+    const Shape sh = gen::zf_shape<T>(gen::step_factors(g.N), g);
     gen::k_z_forward_update<T, P><<<dim3((g.KX + sh.W - 1) / sh.W, g.M, g.batch), sh.W * sh.TT, sh.lds, s>>>(
         static_cast<const cpx<T>*>(x.abuf), g.sphere ? static_cast<const cpx<T>*>(x.akeep) : nullptr, sa,
         static_cast<const cpx<T>*>(x.tw), x.slots, x.dyn, g, gen::step_factors(g.N), sh.W, sh.TT);
@@ -234,7 +235,7 @@ struct GEngine {
     double* mom2 = mom1 + (long long)g.batch * x.nbm * (3 * 6 + 1);
     TimedLaunch tl(x.timer, KID_AUX, s);
     const cpx<T>* st = static_cast<const cpx<T>*>(state);
-    if (flags & 1) k_shell_sums<T><<<dim3(ns, g.batch), 256, 0, s>>>(st, x.slots, g, shells, ns);
+    if (flags & 1) shell_sums(x, st, shells, s);
     if (flags & 2) {
       const int t = moment_threads(g);
       const size_t xl = gen::moment_lds_bytes(g.N, (int)sizeof(cpx<T>), t);
@@ -302,6 +303,7 @@ struct GEngine {
 
   static Ops ops() {
     allow_lds();
+    allow_shell_lds<T>();
     Ops o{};
     o.nsched = 1;
     StepSched& d = o.sched[0];
@@ -324,8 +326,5 @@ struct GEngine {
 };
 
 }  // namespace
-
-Ops ops_general(int precision) { return precision == 32 ? GEngine<float>::ops() : GEngine<double>::ops(); }
-int general_x_lines(int n, int precision) { return gen::x_lines(n, precision == 32 ? 8 : 16); }
 
 }  // namespace psdns
