@@ -17,6 +17,7 @@
 
 #include "common.hpp"
 #include "fft.hpp"
+#include "mem.hpp"
 
 namespace psdns {
 namespace gen {
@@ -390,6 +391,18 @@ inline Shape step_shape(const Factors& f, int csize, int maxt, int waves, int kx
   return best;
 }
 
+// a b for 0 <= a, b < 2^24 (rows and strides in entries): a full-rate multiply where the 32-bit one
+// takes four times as long
+__device__ __forceinline__ int mul24(int a, int b) { return (int)__umul24((unsigned)a, (unsigned)b); }
+// store of a row segment: streamed where a block owns whole 128-byte lines, else left to the L2
+template <typename T>
+__device__ __forceinline__ void put(const Buf<T>& b, uint32_t off, cpx<T> v, int W) {
+  if (W * (int)sizeof(cpx<T>) >= 128)
+    bstore<kPolicyStream>(b, off, 0, v);
+  else
+    bstore<kPolicyCached>(b, off, 0, v);
+}
+
 // root table into LDS; the line buffers follow it
 template <typename T>
 __device__ __forceinline__ cpx<T>* stage_table(cpx<T>* tw, const cpx<T>* __restrict__ tw_g, int N) {
@@ -400,7 +413,9 @@ __device__ __forceinline__ cpx<T>* stage_table(cpx<T>* tw, const cpx<T>* __restr
 }
 
 // ---------------------------------------------------------------------------
-// Column passes of the step (the fields of the tuned kernels' passes).
+// Column passes of the step (the fields of the tuned kernels' passes), addressed by 32-bit offsets
+// into a buffer resource per field: an element cost a 64-bit multiply and add before (200^3 FP64,
+// two scalars: y inverse 381 us against 340, z inverse 192 against 166).
 // z inverse: A fields 0 U1, 1 U2, 2 U3, 3 dz U1, 4 dz U2, 5+2s Phi_s, 6+2s dz Phi_s.
 // ---------------------------------------------------------------------------
 template <typename T>
@@ -418,28 +433,30 @@ k_z_inverse_step(const cpx<T>* __restrict__ st, cpx<T>* __restrict__ abuf, const
   const int kx = blockIdx.x * W + c, kyc = blockIdx.y;
   const bool valid = kx < g.KX;
   const int ky = kyc <= g.K ? kyc : kyc - M;
-  const cpx<T>* sbase = st + (long long)slot * g.F * g.st_field + (long long)kyc * g.PX + kx;
-  cpx<T>* abase = abuf + (long long)slot * g.FA * g.a_field + (long long)kyc * g.PX + kx;
-  const long long row = (long long)M * g.PX;  // state and A rows are this far apart along z
+  const cpx<T>* sbase = st + (long long)slot * g.F * g.st_field;
+  cpx<T>* abase = abuf + (long long)slot * g.FA * g.a_field;
+  const int row = M * g.PX;  // state and A rows are this far apart along z (below 2^24)
+  const int at = kyc * g.PX + kx;
+  auto off = [&](int n) { return (uint32_t)(mul24(n, row) + at) * (uint32_t)sizeof(cpx<T>); };
   for (int f = 0; f < g.F; ++f) {
     const int out = f < 3 ? f : 5 + 2 * (f - 3), dout = f < 2 ? 3 + f : f == 2 ? -1 : out + 1;
-    const cpx<T>* p = sbase + (long long)f * g.st_field;
+    const Buf<T> p = make_buf<T>(sbase + (long long)f * g.st_field);
     for (int d = 0; d < (dout < 0 ? 1 : 2); ++d) {
-      cpx<T>* q = abase + (long long)(d ? dout : out) * g.a_field;
+      const Buf<T> q = make_buf<T>(abase + (long long)(d ? dout : out) * g.a_field);
       fft_io<true, T>(
           [&](int n) {
             const int kz = wave(n, N), kc = compact(kz, g.K, M);
             cpx<T> v = {T(0), T(0)};
             // only retained modes are read: the stage inputs hold nothing defined outside a sphere
             if (valid && kc >= 0 && retained(g, kx, ky, kz)) {
-              v = scale * p[kc * row];
+              v = scale * bload(p, off(kc), 0);
               if (d) v = mul_is(v, T(kz));
               if (shift) v = cmul(v, shift_of(tw, N, kz));
             }
             return v;
           },
           [&](int n, cpx<T> v) {
-            if (valid) q[n * row] = v;
+            if (valid) put(q, off(n), v, W);
           },
           b0, b1, fz, W, c, j, TT, tw);
     }
@@ -462,8 +479,9 @@ k_y_inverse_step(const cpx<T>* __restrict__ abuf, cpx<T>* __restrict__ bbuf, con
   const int c = threadIdx.x % W, j = threadIdx.x / W;
   const int kx = blockIdx.x * W + c, z = blockIdx.y;
   const bool valid = kx < g.KX;
-  const cpx<T>* abase = abuf + (long long)slot * g.FA * g.a_field + a_row(z, 0, M, g.PX) + kx;
-  cpx<T>* bbase = bbuf + (long long)slot * g.FB * g.b_field + (long long)z * N * g.PX + kx;
+  const cpx<T>* abase = abuf + (long long)slot * g.FA * g.a_field + a_row(z, 0, M, g.PX);
+  cpx<T>* bbase = bbuf + (long long)slot * g.FB * g.b_field + (long long)z * N * g.PX;
+  auto off = [&](int n) { return (uint32_t)(mul24(n, g.PX) + kx) * (uint32_t)sizeof(cpx<T>); };
   for (int i = 0; i < g.FB; ++i) {
     // output o from input f, times i ky with dk, minus input f2; a field and its y derivative in turn
     int o, f, f2 = -1;
@@ -479,23 +497,23 @@ k_y_inverse_step(const cpx<T>* __restrict__ abuf, cpx<T>* __restrict__ bbuf, con
       f = 5 + 2 * s + (q == 2 ? 1 : 0);
       dk = q == 1;
     }
-    const cpx<T>* p = abase + (long long)f * g.a_field;
-    const cpx<T>* p2 = abase + (long long)(f2 < 0 ? f : f2) * g.a_field;
-    cpx<T>* q = bbase + (long long)o * g.b_field;
+    const Buf<T> p = make_buf<T>(abase + (long long)f * g.a_field);
+    const Buf<T> p2 = make_buf<T>(abase + (long long)(f2 < 0 ? f : f2) * g.a_field);
+    const Buf<T> q = make_buf<T>(bbase + (long long)o * g.b_field);
     fft_io<true, T>(
         [&](int n) {
           const int ky = wave(n, N), kc = compact(ky, g.K, M);
           cpx<T> v = {T(0), T(0)};
           if (valid && kc >= 0) {
-            v = p[kc * g.PX];
+            v = bload(p, off(kc), 0);
             if (dk) v = mul_is(v, T(ky));
-            if (f2 >= 0) v = v - p2[kc * g.PX];
+            if (f2 >= 0) v = v - bload(p2, off(kc), 0);
             if (shift) v = cmul(v, shift_of(tw, N, ky));
           }
           return v;
         },
         [&](int n, cpx<T> v) {
-          if (valid) q[n * g.PX] = v;
+          if (valid) put(q, off(n), v, W);
         },
         b0, b1, fy, W, c, j, TT, tw);
   }
@@ -518,17 +536,18 @@ k_y_forward_step(const cpx<T>* __restrict__ bbuf, cpx<T>* __restrict__ aout, int
   const int c = threadIdx.x % W, j = threadIdx.x / W;
   const int kx = blockIdx.x * W + c, z = blockIdx.y;
   const bool valid = kx < g.KX;
-  const cpx<T>* bbase = bbuf + (long long)slot * g.FB * g.b_field + (long long)z * N * g.PX + kx;
-  cpx<T>* obase = aout + (long long)slot * a_fields * g.a_field + a_row(z, 0, M, g.PX) + kx;
+  const cpx<T>* bbase = bbuf + (long long)slot * g.FB * g.b_field + (long long)z * N * g.PX;
+  cpx<T>* obase = aout + (long long)slot * a_fields * g.a_field + a_row(z, 0, M, g.PX);
+  auto off = [&](int n) { return (uint32_t)(mul24(n, g.PX) + kx) * (uint32_t)sizeof(cpx<T>); };
   for (int f = 0; f < nf; ++f) {
-    const cpx<T>* p = bbase + (long long)f * g.b_field;
-    cpx<T>* q = obase + (long long)f * g.a_field;
-    fft_io<false, T>([&](int n) { return valid ? p[n * g.PX] : cpx<T>{T(0), T(0)}; },
+    const Buf<T> p = make_buf<T>(bbase + (long long)f * g.b_field);
+    const Buf<T> q = make_buf<T>(obase + (long long)f * g.a_field);
+    fft_io<false, T>([&](int n) { return valid ? bload(p, off(n), 0) : cpx<T>{T(0), T(0)}; },
                      [&](int n, cpx<T> v) {
                        const int ky = wave(n, N), kc = compact(ky, g.K, M);
                        if (!valid || kc < 0) return;
                        if (shift) v = cmul(v, conj(shift_of(tw, N, ky)));
-                       q[kc * g.PX] = v;
+                       put(q, off(kc), v, W);
                      },
                      b0, b1, fy, W, c, j, TT, tw);
   }
@@ -636,6 +655,7 @@ k_y_inverse(const cpx<T>* __restrict__ abuf, cpx<T>* __restrict__ bbuf, const cp
 // before it, so that at most six fields are live.
 // ---------------------------------------------------------------------------
 constexpr int kXThreads = 256;
+constexpr int kShortPositions = 9;  // positions per lane of a line that shares its wavefront, at most
 constexpr int kMaxPositions = 16;  // N <= 1024: 64 lanes per x line, 64 or more threads per z column
 
 // Launch shape of the x pass: TL lanes per line (16, 32 or 64: a line stays inside a wavefront), lw
@@ -660,7 +680,7 @@ inline XShape x_shape(const Factors& f, int csize, long long lines) {
   double least = 0.0;
   for (int TL = 64; TL >= 16; TL /= 2) {
     const int P = (N + TL - 1) / TL;
-    if (TL < 64 && P > (csize == 8 ? 9 : 8)) break;
+    if (TL < 64 && P > (csize == 8 ? kShortPositions : 8)) break;
     double turns = 0.0;
     for (int i = 0; i < f.nst; ++i) turns += (double)((N / f.r[i] + TL - 1) / TL) * radix_cost(f.r[i]);
     const long long waves = (lines * TL + 63) / 64;
@@ -685,10 +705,13 @@ constexpr int x_waves() {
   return sizeof(T) == 4 ? (P <= 4 ? 4 : P <= 12 ? 3 : 2) : (P <= 10 ? 2 : 1);
 }
 
-template <typename T, int P>
+// FULL: 64 lanes per line, known when compiled (520^3 FP32: 4.3 ms; with TL at run time 28 registers
+// spill, 5.4)
+template <typename T, int P, bool FULL>
 __global__ void __launch_bounds__(kXThreads, (x_waves<T, P>()))
 k_x_pass(cpx<T>* __restrict__ bbuf, const cpx<T>* __restrict__ tw_g, const SlotDev* __restrict__ slots,
-         DynDev* __restrict__ dyn, Geom g, Factors fx, int TL, int shift, int umax) {
+         DynDev* __restrict__ dyn, Geom g, Factors fx, int lanes, int shift, int umax) {
+  const int TL = FULL ? 64 : lanes;
   extern __shared__ char lds_raw[];
   const int N = g.N, S = g.S, K = g.K;
   const int nt = (int)root_table_entries(N);
@@ -701,7 +724,8 @@ k_x_pass(cpx<T>* __restrict__ bbuf, const cpx<T>* __restrict__ tw_g, const SlotD
   const int lw = blockDim.x / TL, li = threadIdx.x / TL, j = threadIdx.x % TL;
   // z * N + y; lanes past the last line repeat it and store nothing
   const long long line0 = (long long)blockIdx.x * lw + li, lines = (long long)N * N;
-  const bool own = line0 < lines;
+  if (FULL && line0 >= lines) return;
+  const bool own = FULL || line0 < lines;
   const long long line = own ? line0 : lines - 1;
   cpx<T>* b0 = tw + nt + (size_t)li * 2 * N;
   cpx<T>* b1 = b0 + N;
@@ -1024,14 +1048,16 @@ k_z_forward_update(const cpx<T>* __restrict__ abuf, const cpx<T>* __restrict__ a
     q.rhs += sa.stage < 0 ? foff : 0;
     return q;
   };
+  const int row = M * g.PX, rat = kyc * g.PX + kx;
+  auto off = [&](int n) { return (uint32_t)(mul24(n, row) + rat) * (uint32_t)sizeof(cpx<T>); };
   const int S = g.S, per = kslot ? 2 : 1;
   cpx<T> v[P], c1[P], c2[P];
   for (int t = 0; t < (S + 3) * per; ++t) {
     const int fi = t / per, half = t % per;
     const int f = fi < S ? 3 + fi : fi - S;  // A field: scalar fi, or velocity component fi - S
-    const cpx<T>* src = (half ? kslot : aslot) + (long long)f * g.a_field;
+    const Buf<T> src = make_buf<T>((half ? kslot : aslot) + (long long)f * g.a_field);
     const cpx<T>* r = fft_in<false, BlockSync, T>(
-        [&](int n) { return valid ? src[a_row(n, kyc, M, g.PX) + kx] : cpx<T>{T(0), T(0)}; }, b0, b1, fz, W, c, j, TT,
+        [&](int n) { return valid ? bload(src, off(n), 0) : cpx<T>{T(0), T(0)}; }, b0, b1, fz, W, c, j, TT,
         tw);
 #pragma unroll
     for (int m = 0; m < P; ++m) {

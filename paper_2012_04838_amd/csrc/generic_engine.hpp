@@ -59,8 +59,15 @@ struct GEngine {
   static void launch_x(const Ctx& x, const gen::XShape& sh, const Factors& f, int shift, int umax, hipStream_t s) {
     const Geom& g = x.g;
     const long long lines = (long long)g.N * g.N;
-    gen::k_x_pass<T, P><<<dim3((unsigned)((lines + sh.lw - 1) / sh.lw), g.batch), sh.TL * sh.lw, sh.lds, s>>>(
-        static_cast<cpx<T>*>(x.bbuf), static_cast<const cpx<T>*>(x.tw), x.slots, x.dyn, g, f, sh.TL, shift, umax);
+    const dim3 grid((unsigned)((lines + sh.lw - 1) / sh.lw), g.batch);
+    const int threads = sh.TL * sh.lw;
+    cpx<T>* B = static_cast<cpx<T>*>(x.bbuf);
+    const cpx<T>* tw = static_cast<const cpx<T>*>(x.tw);
+    if (sh.TL == 64) {
+      gen::k_x_pass<T, P, true><<<grid, threads, sh.lds, s>>>(B, tw, x.slots, x.dyn, g, f, 64, shift, umax);
+    } else if constexpr (P <= gen::kShortPositions) {
+      gen::k_x_pass<T, P, false><<<grid, threads, sh.lds, s>>>(B, tw, x.slots, x.dyn, g, f, sh.TL, shift, umax);
+    }
   }
   // the line-moment kernel of the statistics: up to 256 threads per line
   static int moment_threads(const Geom& g) {
@@ -152,7 +159,8 @@ struct GEngine {
       if (stage == 0 && p == 0) {
         TimedLaunch tl(x.timer, KID_DT, s);
         k_step_dt<<<g.batch, 64, 0, s>>>(x.slots, x.dyn, g, dt_arg);
-        k_stochastic_update<T><<<g.batch, 256, 0, s>>>(static_cast<const cpx<T>*>(state), x.slots, x.dyn, x.fband, g);
+        if (x.stochastic)
+          k_stochastic_update<T><<<g.batch, 256, 0, s>>>(static_cast<const cpx<T>*>(state), x.slots, x.dyn, x.fband, g);
       }
       {
         TimedLaunch tl(x.timer, KID_YFWD, s);
@@ -292,8 +300,11 @@ struct GEngine {
     for (int p = 1; p <= gen::kMaxPositions; ++p)
       with_positions(p, [&](auto q) {
         constexpr int P = decltype(q)::value;
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&gen::k_x_pass<T, P>),
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&gen::k_x_pass<T, P, true>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, b);
+        if constexpr (P <= gen::kShortPositions)
+          (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&gen::k_x_pass<T, P, false>),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, b);
         (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&gen::k_z_forward_update<T, P>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, b);
       });
