@@ -523,8 +523,8 @@ k_step_dt(const SlotDev* __restrict__ slots, DynDev* __restrict__ dyn, Geom g, d
 // exp(i pi ky / N).
 // With fsin (the stage input) the grid has one more row, the first: its first block of each
 // slot computes the forcing amplitude, which the z pass of the stage reads.  A small grid is
-// bound by its launches, and this one rides along (32^3 FP64: six launches fewer of 22 per step
-// with the step size in the y forward, 193 us a step to 157).
+// bound by its launches, and this one rides along (with the step size in the y forward, six
+// launches fewer of 22 per step; 32^3 FP64, together with fft.hpp's butterflies: 200 us a step to 180).
 // ---------------------------------------------------------------------------
 template <int N, typename T, int V, int DL = 0>
 __global__ void PSDNS_COL_BOUNDS(Cfg<N, T, V>::COL_THREADS)
@@ -2284,14 +2284,6 @@ k_convert(cpx<T>* __restrict__ st, cpx<T>* __restrict__ canon, Geom g, int slot)
 // per shell: [0] sum w |u|^2/2, [1] sum w (|k|^2 |u|^2 + |k.u|^2),
 // per scalar s: [2+3s] sum w |phi|^2/2, [3+3s] sum w |k|^2 |phi|^2, [4+3s] sum w Re(conj(phi) g_s.u)
 __host__ __device__ inline int shell_quantities(int S) { return 2 + 3 * S; }
-
-__device__ __forceinline__ int isqrt_floor(long long v) {
-  if (v <= 0) return 0;
-  long long r = (long long)sqrt((double)v);
-  while (r * r > v) --r;
-  while ((r + 1) * (r + 1) <= v) ++r;
-  return (int)r;
-}
 
 // Blocks of the shell sums per slot, for m^2 rows of the state.
 inline int shell_blocks(int m) {

@@ -164,7 +164,8 @@ __device__ __forceinline__ cpx<T>* fft(cpx<T>* b0, cpx<T>* b1, const Factors& f,
 // Transforms of the step kernels.  Their first stage takes its butterflies' inputs straight
 // from a functor (global memory) and their last one hands its outputs to one, so that a column
 // makes nst - 1 round trips through LDS with one barrier each, against nst + 1 with two more
-// barriers where every line is staged in and out (520^3 FP32: y inverse 2.61 ms).  Odd radices
+// barriers where every line is staged in and out (520^3 FP32, one scalar: y inverse 2.61
+// ms, 2.16 with this, the launch shapes and the addressing below).  Odd radices
 // come first: on a single line their stage writes R entries apart, free of bank conflicts for odd
 // R (radix 8 first: sixteen lanes on one bank), and the global loads of a wide first butterfly
 // are all in flight at once.  Power-of-two radices take the factors of fft.hpp's dft.
