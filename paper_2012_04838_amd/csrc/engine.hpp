@@ -356,7 +356,7 @@ k_z_inverse(const cpx<T>* __restrict__ st, cpx<T>* __restrict__ abuf, const cpx<
   const int slot = cb.slot;
   if (!slots[slot].active) return;
   if constexpr (DL) stage_shift<N, false>(sph, tw_g);
-  stage_twiddles<N>(stw, tw_g);
+  stage_twiddles<N, E>(stw, tw_g);
   const cpx<T>* tw = stw;
   const int c = threadIdx.x % W;
   const int j = threadIdx.x / W;
@@ -551,7 +551,7 @@ k_y_inverse(const cpx<T>* __restrict__ abuf, cpx<T>* __restrict__ bbuf, const cp
     return;
   }
   if constexpr (DL) stage_shift<N, false>(sph, tw_g);
-  stage_twiddles<N>(stw, tw_g);
+  stage_twiddles<N, E>(stw, tw_g);
   const cpx<T>* tw = stw;
   const int c = threadIdx.x % W;
   const int j = threadIdx.x / W;
@@ -806,14 +806,14 @@ k_x_pass(cpx<T>* __restrict__ bbuf, const cpx<T>* __restrict__ tw_g, const SlotD
   __shared__ cpx<T> xch[XL::kXch > 0 ? XL::kXch * C::X_THREADS : 1];
   const int slot = blockIdx.y;
   if (!slots[slot].active) return;
-  stage_twiddles<N>(stw, tw_g);
+  stage_twiddles<N, E>(stw, tw_g);
   const int li = threadIdx.x / TT;
   const int j = threadIdx.x % TT;
-  // FP32 up to N = 512: the lane's twiddles live in registers for all nine transforms
-  // of the line; FP64, and the 16-element lines of N = 1024, keep them in LDS to leave
+  // FP32 up to N = 512: the lane's factors live in registers for all nine transforms
+  // of the line; FP64 and the lines of N = 1024 (18 factors a lane) keep them in LDS to leave
   // registers for the line data.
   constexpr bool kLong = E > 8;
-  constexpr bool kRegTw = sizeof(T) == 4 && !kLong && C::D.xreg;
+  constexpr bool kRegTw = sizeof(T) == 4 && !kLong && N <= 512 && C::D.xreg;
   // FP32 short lines load every input up front; FP64 and 16-element lines load u3/omega1
   // and u1/u2 only when their transform comes (registers)
   constexpr bool kLate = kLong || sizeof(T) == 8;
@@ -1100,7 +1100,7 @@ k_plane(cpx<T>* __restrict__ abuf, const cpx<T>* __restrict__ tw_g, const SlotDe
     return;
   }
   const int z = blockIdx.x - 1;
-  stage_twiddles<N>(stw, tw_g);
+  stage_twiddles<N, E>(stw, tw_g);
   // column role: the threads past the pair's columns repeat the first ones' work and store nothing
   const bool own = (int)threadIdx.x < C::ITEMS;
   const int item = own ? threadIdx.x : threadIdx.x - C::ITEMS;
@@ -1318,7 +1318,7 @@ k_y_forward(const cpx<T>* __restrict__ bbuf, cpx<T>* __restrict__ abuf, const cp
     return;
   }
   if constexpr (DL) stage_shift<N, true>(sph, tw_g);
-  stage_twiddles<N>(stw, tw_g);
+  stage_twiddles<N, E>(stw, tw_g);
   const cpx<T>* tw = stw;
   const int c = threadIdx.x % W;
   const int j = threadIdx.x / W;
@@ -1544,7 +1544,7 @@ k_z_forward_update(cpx<T>* __restrict__ abuf, StageArgs<T> sa, const cpx<T>* __r
     }
   }
   if constexpr (DL) stage_shift<N, true>(sph, tw_g);
-  stage_twiddles<N>(stw, tw_g);  // its barrier also covers ez and sph
+  stage_twiddles<N, E>(stw, tw_g);  // its barrier also covers ez and sph
   const cpx<T>* tw = stw;
   const int c = threadIdx.x % W;
   const int j = threadIdx.x / W;
@@ -1864,7 +1864,7 @@ k_z_forward_pressure(const cpx<T>* __restrict__ abuf, cpx<T>* __restrict__ pout,
   __shared__ cpx<T> stw[N];
   const int slot = blockIdx.z;
   if (!slots[slot].active) return;
-  stage_twiddles<N>(stw, tw_g);
+  stage_twiddles<N, E>(stw, tw_g);
   const cpx<T>* tw = stw;
   const int c = threadIdx.x % W;
   const int j = threadIdx.x / W;
@@ -1887,6 +1887,10 @@ k_z_forward_pressure(const cpx<T>* __restrict__ abuf, cpx<T>* __restrict__ pout,
   load_fwd(0);
 #pragma unroll
   for (int m = 0; m < E; ++m) kdc[m] = T(kx) * v[m];
+  // formed here: left to itself the compiler keeps c1 through the next transform instead (256^3
+  // FP32: 138 registers, three waves per SIMD, against 117 and four)
+#pragma unroll
+  for (int m = 0; m < E; ++m) asm volatile("" : "+v"(kdc[m].x), "+v"(kdc[m].y));
   load_fwd(1);
 #pragma unroll
   for (int m = 0; m < E; ++m) kdc[m] = kdc[m] + T(ky) * v[m];
@@ -2448,7 +2452,7 @@ k_stats_z(const cpx<T>* __restrict__ st, cpx<T>* __restrict__ abuf, const cpx<T>
   __shared__ cpx<T> smem[W * N];
   __shared__ cpx<T> stw[N];
   const int slot = blockIdx.z;
-  stage_twiddles<N>(stw, tw_g);
+  stage_roots<N>(stw, tw_g);
   const cpx<T>* tw = stw;
   const int c = threadIdx.x % W, j = threadIdx.x / W;
   const int kx = blockIdx.x * W + c, kyc = blockIdx.y;
@@ -2489,7 +2493,7 @@ k_stats_y(const cpx<T>* __restrict__ abuf, cpx<T>* __restrict__ bbuf, const cpx<
   __shared__ cpx<T> smem[W * N];
   __shared__ cpx<T> stw[N];
   const int slot = blockIdx.z;
-  stage_twiddles<N>(stw, tw_g);
+  stage_roots<N>(stw, tw_g);
   const cpx<T>* tw = stw;
   const int c = threadIdx.x % W, j = threadIdx.x / W;
   const int kx = blockIdx.x * W + c, z = blockIdx.y;
@@ -2531,7 +2535,7 @@ k_x_moments(const cpx<T>* __restrict__ bbuf, const cpx<T>* __restrict__ tw_g, Ge
   __shared__ double red[C::X_THREADS];
   __shared__ cpx<T> xch[XL::kXch > 0 ? XL::kXch * C::X_THREADS : 1];
   const int slot = blockIdx.y;
-  stage_twiddles<N>(stw, tw_g);
+  stage_roots<N>(stw, tw_g);
   const cpx<T>* tw = stw;
   const XL xl(threadIdx.x, xch);
   const int li = threadIdx.x / TT, j = xl.j;

@@ -196,13 +196,13 @@ inline Factors step_factors(int N) {
   return f;
 }
 
-template <int R, typename T>
+template <typename T>
 struct TabTw {
   const cpx<T>* tw;
-  int at, nr;  // kv N / (NS R) and N / R
-  template <int LEN, int K>
+  int at;
+  template <int I>
   __device__ __forceinline__ cpx<T> get() const {
-    return tw[(at + K * nr) * (R / LEN)];
+    return tw[(I + 1) * at];
   }
 };
 
@@ -225,7 +225,7 @@ __device__ __forceinline__ void radix(cpx<T> (&a)[R], const cpx<T>* tw, int at, 
   } else if constexpr (FIRST) {
     dft<R, INV>(a);
   } else {
-    dft<R, INV>(a, TabTw<R, T>{tw, at, N / R});
+    dft<R, INV>(a, TabTw<T>{tw, at});
   }
 }
 
