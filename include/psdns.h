@@ -267,7 +267,7 @@ psdns_status psdns_step_noalloc(psdns_plan* plan, void* state, double dt, int32_
  * (state, ws, dt) and then replays that graph once per step; a different state, workspace
  * or dt re-captures.  Slot parameters and active flags are read by the kernels at replay
  * time, so psdns_set_slot needs no re-capture, except that switching slots into or out of
- * PSDNS_FORCING_HOLD or the stochastic forcings changes the step structure and re-captures.  Steps on the default (NULL) stream are
+ * PSDNS_FORCING_HOLD changes the step structure and re-captures.  Steps on the default (NULL) stream are
  * launched directly.  Timing events are not recorded for replayed steps. */
 psdns_status psdns_set_graph(psdns_plan* plan, int32_t enable);
 

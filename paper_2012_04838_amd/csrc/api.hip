@@ -282,7 +282,6 @@ struct psdns_plan {
   const void* graph_ws = nullptr;
   double graph_dt = 0.0;
   bool graph_hold = false;  // captured with the hold forcing's step structure
-  bool graph_stoch = false; // captured with the update of the stochastic forcings
   bool graph_expl = false;  // captured with the unfused stages of an explicit-integrator slot
   bool general = false;     // runs the general kernels (ops_general)
   int psched[kNumPasses] = {0, 0, 0, 0, 0};  // schedule of each pass (psdns_set_pass_schedules)
@@ -310,9 +309,6 @@ Ctx make_ctx(psdns_plan* plan, void* ws) {
   c.bbuf = w + plan->L.off_bbuf;
   c.akeep = plan->L.g.sphere ? w + plan->L.off_akeep : nullptr;
   c.timer = plan->timer;
-  for (const SlotDev& d : plan->slots_host)
-    c.stochastic = c.stochastic ||
-                   (d.active && (d.forcing == PSDNS_FORCING_STOCHASTIC || d.forcing == PSDNS_FORCING_ALVELIUS));
   return c;
 }
 
@@ -403,7 +399,7 @@ psdns_status run_steps(psdns_plan* plan, void* state, void* ws, double dt, int n
   };
   if (allow_graph && s != nullptr && nsteps > 0) {
     if (!plan->graph_exec || plan->graph_state != state || plan->graph_ws != ws || plan->graph_dt != dt ||
-        plan->graph_hold != hold || plan->graph_expl != expl || plan->graph_stoch != c.stochastic) {
+        plan->graph_hold != hold || plan->graph_expl != expl) {
       if (plan->graph_exec) {
         HIP_TRY(hipGraphExecDestroy(plan->graph_exec));
         plan->graph_exec = nullptr;
@@ -430,7 +426,6 @@ psdns_status run_steps(psdns_plan* plan, void* state, void* ws, double dt, int n
       plan->graph_ws = ws;
       plan->graph_hold = hold;
       plan->graph_expl = expl;
-      plan->graph_stoch = c.stochastic;
       plan->graph_dt = dt;
     }
     // the captured step expects the z inverse of y_n: run it once, then replay

@@ -146,7 +146,6 @@ struct Ctx {
   int spectra_rec;         // doubles per slot of the spectra record
   Timer* timer;            // may be null
   int psched[kNumPasses];  // schedule of each pass (Ops::rhs_mixed)
-  bool stochastic;         // an active slot has a stochastic forcing (k_stochastic_update is launched)
 };
 
 // One evaluation of the nonlinear right-hand side at stage_in followed by the stage

@@ -498,7 +498,7 @@ static __device__ __forceinline__ void step_dt(DynDev& d, const Geom& g, double 
   d.umax = 0ull;  // the next step's stage 0 starts a fresh grid maximum
 }
 
-// the same as launches of their own, for the general kernels
+// the same as a launch of its own, for the general kernels
 template <typename T>
 __global__ void __launch_bounds__(256)
 k_forcing_amplitude(const cpx<T>* __restrict__ sin, const SlotDev* __restrict__ slots, DynDev* __restrict__ dyn,
@@ -507,11 +507,6 @@ k_forcing_amplitude(const cpx<T>* __restrict__ sin, const SlotDev* __restrict__ 
   const int slot = blockIdx.x;
   if (!slots[slot].active) return;
   forcing_block(sin, slots[slot], dyn[slot], g, slot, red);
-}
-static __global__ void __launch_bounds__(64)
-k_step_dt(const SlotDev* __restrict__ slots, DynDev* __restrict__ dyn, Geom g, double dt_arg) {
-  const int slot = blockIdx.x;
-  if (slots[slot].active && threadIdx.x == 0) step_dt(dyn[slot], g, dt_arg);
 }
 
 // ---------------------------------------------------------------------------
@@ -1291,14 +1286,11 @@ k_plane(cpx<T>* __restrict__ abuf, const cpx<T>* __restrict__ tw_g, const SlotDe
 // ---------------------------------------------------------------------------
 // y forward: columns along y at fixed (z, kx-tile); keeps |ky| <= K.
 // The next field's loads are issued before the current field is transformed.
-// With dyn (stage 0 of a step) the grid has one more row, the first: its first block of each
-// slot sets the step size from the x pass's maximum and advances the step record.
 // ---------------------------------------------------------------------------
 template <int N, typename T, int V, int DL = 0>
 __global__ void PSDNS_YF_BOUNDS(Cfg<N, T, V>::COL_THREADS)
 k_y_forward(const cpx<T>* __restrict__ bbuf, cpx<T>* __restrict__ abuf, const cpx<T>* __restrict__ tw_g,
-            const SlotDev* __restrict__ slots, Geom g, DynDev* __restrict__ dyn, double dt_arg, int shift = 0,
-            int afields = 0) {
+            const SlotDev* __restrict__ slots, Geom g, int shift = 0, int afields = 0) {
   using C = Cfg<N, T, V>;
   constexpr int W = C::W, E = C::EC, TT = C::TC;
   constexpr int K = kmax<N, DL>();
@@ -1308,22 +1300,17 @@ k_y_forward(const cpx<T>* __restrict__ bbuf, cpx<T>* __restrict__ abuf, const cp
   __shared__ cpx<T> smem[L::kEntries];
   __shared__ cpx<T> stw[N];
   __shared__ cpx<T> sph[DL ? N : 1];
-  const int extra = dyn ? 1 : 0;
-  const ColBlock cb = col_block<C::Col::PAIR>((g.KX + W - 1) / W, N + extra);
+  const ColBlock cb = col_block<C::Col::PAIR>((g.KX + W - 1) / W, N);
   if (!cb.ok) return;
   const int slot = cb.slot;
   if (!slots[slot].active) return;
-  if (cb.row < extra) {
-    if (cb.tile == 0 && threadIdx.x == 0) step_dt(dyn[slot], g, dt_arg);
-    return;
-  }
   if constexpr (DL) stage_shift<N, true>(sph, tw_g);
   stage_twiddles<N, E>(stw, tw_g);
   const cpx<T>* tw = stw;
   const int c = threadIdx.x % W;
   const int j = threadIdx.x / W;
   const int kx = cb.tile * W + c;
-  const int z = cb.row - extra;
+  const int z = cb.row;
   const bool valid = kx < g.KX;
   const typename L::View lds{smem + c};
   const uint32_t rsb = (uint32_t)g.PX * CS;
@@ -1720,7 +1707,7 @@ k_z_forward_update(cpx<T>* __restrict__ abuf, StageArgs<T> sa, const cpx<T>* __r
     average(2, c3);
 #endif
     if ((sp.forcing == PSDNS_FORCING_STOCHASTIC || sp.forcing == PSDNS_FORCING_ALVELIUS) && valid) {
-      // the stochastic forcing term of the band modes (solenoidal, from k_stochastic_update)
+      // the stochastic forcing term of the band modes (solenoidal, from k_step_dt)
       // joins the transformed product; the projection below leaves it unchanged
       int kfs = 0;
       while ((double)(kfs + 1) * (kfs + 1) <= sp.kf2) ++kfs;
@@ -2046,13 +2033,20 @@ __device__ void alvelius_mode(int kx, int ky, int kz, const cpx<T>* __restrict__
   }
 }
 
+// Step size and step record of one slot per block, then the update of its stochastic forcing's band
+// table where the slot has one.  The slot table decides here, on the device, so that a step recorded
+// in a graph follows a later psdns_set_slot; one launch for both, as a small grid is bound by its
+// launches.
 template <typename T>
 __global__ void __launch_bounds__(256)
-k_stochastic_update(const cpx<T>* __restrict__ yn, const SlotDev* __restrict__ slots, const DynDev* __restrict__ dyn,
-                    double* __restrict__ fband, Geom g) {
+k_step_dt(const cpx<T>* __restrict__ yn, const SlotDev* __restrict__ slots, DynDev* dyn, double* __restrict__ fband,
+          Geom g, double dt_arg) {
   const int slot = blockIdx.x;
   const SlotDev& sp = slots[slot];
-  if (!sp.active || (sp.forcing != PSDNS_FORCING_STOCHASTIC && sp.forcing != PSDNS_FORCING_ALVELIUS)) return;
+  if (!sp.active) return;
+  if (threadIdx.x == 0) step_dt(dyn[slot], g, dt_arg);
+  if (sp.forcing != PSDNS_FORCING_STOCHASTIC && sp.forcing != PSDNS_FORCING_ALVELIUS) return;
+  __syncthreads();
   const bool alv = sp.forcing == PSDNS_FORCING_ALVELIUS;
   int kf = 0;
   while ((double)(kf + 1) * (kf + 1) <= sp.kf2) ++kf;
@@ -2727,6 +2721,13 @@ struct TimedLaunch {
   }
 };
 
+// after the x pass of stage 0: step size, step record and stochastic band tables
+template <typename T>
+void step_record(const Ctx& x, const void* state, double dt_arg, hipStream_t s) {
+  TimedLaunch tl(x.timer, KID_DT, s);
+  k_step_dt<T><<<x.g.batch, 256, 0, s>>>(static_cast<const cpx<T>*>(state), x.slots, x.dyn, x.fband, x.g, dt_arg);
+}
+
 // The passes of one right-hand-side evaluation and stage update with schedule V.  Every
 // schedule reads and writes the same buffers in the same layouts, so a stage may take
 // each pass from a different schedule (Stage below).
@@ -2756,12 +2757,11 @@ struct Step {
     k_x_pass<N, T, VX><<<dim3(kXBlocks, g.batch), C::X_THREADS, 0, s>>>(
         static_cast<cpx<T>*>(x.bbuf), static_cast<const cpx<T>*>(x.tw), x.slots, x.dyn, g, mode);
   }
-  // set_dt (stage 0): also the step size and the step record
-  static void y_forward(const Ctx& x, bool set_dt, double dt_arg, hipStream_t s) {
+  static void y_forward(const Ctx& x, hipStream_t s) {
     TimedLaunch tl(x.timer, KID_YFWD, s);
-    k_y_forward<N, T, VC><<<dim3(ntile(x.g), N + (set_dt ? 1 : 0), x.g.batch), C::COL_THREADS, 0, s>>>(
+    k_y_forward<N, T, VC><<<dim3(ntile(x.g), N, x.g.batch), C::COL_THREADS, 0, s>>>(
         static_cast<const cpx<T>*>(x.bbuf), static_cast<cpx<T>*>(x.abuf), static_cast<const cpx<T>*>(x.tw), x.slots,
-        x.g, set_dt ? x.dyn : nullptr, dt_arg);
+        x.g);
   }
   // fuse: every stage of a multi-step call, the stage fixed at compile time
   static void z_forward(const Ctx& x, const StageArgs<T>& sa, int stage, bool fuse, hipStream_t s) {
@@ -2829,23 +2829,15 @@ struct Stage {
           k_plane<N, T><<<dim3(N + 1, g.batch), PlaneCfg<N, T>::THREADS, 0, s>>>(
               static_cast<cpx<T>*>(x.abuf), static_cast<const cpx<T>*>(x.tw), x.slots, x.dyn, g, sin, want_max);
         }
-        if (stage == 0) {
-          TimedLaunch tl(x.timer, KID_DT, s);
-          k_step_dt<<<g.batch, 64, 0, s>>>(x.slots, x.dyn, g, dt_arg);
-        }
+        if (stage == 0) step_record<T>(x, state, dt_arg, s);
       }
     }
     if (!plane) {
       with_sched<N>(x.psched[kPassYInverse], [&](auto v) { Step<N, T, decltype(v)::value>::y_inverse(x, sin, s); });
       with_sched<N>(x.psched[kPassX],
                     [&](auto v) { Step<N, T, decltype(v)::value>::x_pass(x, g, want_max ? kXMax : 0, s); });
-      with_sched<N>(x.psched[kPassYForward],
-                    [&](auto v) { Step<N, T, decltype(v)::value>::y_forward(x, stage == 0, dt_arg, s); });
-    }
-    if (stage == 0 && x.stochastic) {
-      // returns at once for slots without the stochastic forcing
-      TimedLaunch tl(x.timer, KID_DT, s);
-      k_stochastic_update<T><<<g.batch, 256, 0, s>>>(static_cast<const cpx<T>*>(state), x.slots, x.dyn, x.fband, g);
+      if (stage == 0) step_record<T>(x, state, dt_arg, s);
+      with_sched<N>(x.psched[kPassYForward], [&](auto v) { Step<N, T, decltype(v)::value>::y_forward(x, s); });
     }
     StageArgs<T> sa;
     sa.yn = static_cast<cpx<T>*>(state);
@@ -2895,15 +2887,11 @@ struct Stage {
         k_x_pass<N, T, kPhaseX, 1><<<dim3(Step<N, T, kPhaseX>::kXBlocks, g.batch), Cfg<N, T, kPhaseX>::X_THREADS, 0,
                                      s>>>(B, tw, x.slots, x.dyn, g, mode);
       }
-      const bool set_dt = stage == 0 && p == 0;
+      if (stage == 0 && p == 0) step_record<T>(x, state, dt_arg, s);
       {
         TimedLaunch tl(x.timer, KID_YFWD, s);
-        k_y_forward<N, T, 0, 1><<<dim3(nt, N + (set_dt ? 1 : 0), g.batch), C::COL_THREADS, 0, s>>>(
-            B, p ? A : keep, tw, x.slots, g, set_dt ? x.dyn : nullptr, dt_arg, p, p ? g.FA : g.F);
-      }
-      if (set_dt && x.stochastic) {
-        TimedLaunch tl(x.timer, KID_DT, s);
-        k_stochastic_update<T><<<g.batch, 256, 0, s>>>(static_cast<const cpx<T>*>(state), x.slots, x.dyn, x.fband, g);
+        k_y_forward<N, T, 0, 1><<<dim3(nt, N, g.batch), C::COL_THREADS, 0, s>>>(B, p ? A : keep, tw, x.slots, g, p,
+                                                                                  p ? g.FA : g.F);
       }
     }
     StageArgs<T> sa;
@@ -2999,7 +2987,7 @@ struct Engine {
     k_x_pass<N, T, 0><<<dim3(gp.nblk_x, gp.batch), C0::X_THREADS, 0, s>>>(B, tw, x.slots, x.dyn, gp, kXPressure);
     Geom gy = gp;
     gy.F = 4;  // c1, c2, c3, |u|^2/2
-    k_y_forward<N, T, 0><<<dim3(gx, N, gp.batch), C0::COL_THREADS, 0, s>>>(B, A, tw, x.slots, gy, nullptr, 0.0);
+    k_y_forward<N, T, 0><<<dim3(gx, N, gp.batch), C0::COL_THREADS, 0, s>>>(B, A, tw, x.slots, gy);
     k_z_forward_pressure<N, T><<<dim3(ntile, gp.M, gp.batch), C0::COL_THREADS, 0, s>>>(A, P, tw, x.slots, gp);
     const long long per = (long long)N * N * (N / 2 + 1);
     k_fill_zero<T><<<(unsigned)((per * gp.batch + 255) / 256), 256, 0, s>>>(static_cast<cpx<T>*>(canon),

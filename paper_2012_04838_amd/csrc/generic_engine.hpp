@@ -156,12 +156,7 @@ struct GEngine {
         // Eq. (10) takes the maximum over the grid points themselves: unshifted pass only
         x_pass(x, shift, want_max && p == 0, s);
       }
-      if (stage == 0 && p == 0) {
-        TimedLaunch tl(x.timer, KID_DT, s);
-        k_step_dt<<<g.batch, 64, 0, s>>>(x.slots, x.dyn, g, dt_arg);
-        if (x.stochastic)
-          k_stochastic_update<T><<<g.batch, 256, 0, s>>>(static_cast<const cpx<T>*>(state), x.slots, x.dyn, x.fband, g);
-      }
+      if (stage == 0 && p == 0) step_record<T>(x, state, dt_arg, s);
       {
         TimedLaunch tl(x.timer, KID_YFWD, s);
         const bool keep = g.sphere && p == 0;
