@@ -4,24 +4,40 @@
 the caller's state and selects the fastest.  This module keeps that choice per (device,
 N, S, precision, batch) in a JSON file, so a plan of a known shape starts with its
 schedule without re-timing.  Keys also carry a signature of the compiled schedule
-table, so a rebuilt library with different schedules does not reuse stale entries.
+table and of the library file itself, so a rebuilt library with other kernels does not reuse
+stale entries: timings belong to the kernels they were taken with, and a schedule's description
+(tile and radix choices) does not say all that its kernels do.
 """
 from __future__ import annotations
 
+import functools
 import hashlib
 import json
 import os
 import tempfile
 from typing import Optional
 
+from . import psdns
+
 DEFAULT_PATH = os.environ.get("PSDNS_TUNE_CACHE",
                               os.path.join(os.path.expanduser("~"), ".cache", "psdns", "tune.json"))
 
 
+@functools.lru_cache(maxsize=None)
+def library_digest(path: str) -> str:
+    """Digest of the library file (read once per process, which also loads it once)."""
+    try:
+        with open(path, "rb") as f:
+            return hashlib.sha256(f.read()).hexdigest()
+    except OSError:
+        return "none"
+
+
 def schedule_signature(plan) -> str:
-    """Digest of the plan's compiled schedule descriptions."""
+    """Digest of the plan's compiled schedule descriptions and of the kernels behind them."""
     desc = [plan.schedule_info(i) for i in range(plan.n_schedules)]
-    return hashlib.sha256(json.dumps(desc, sort_keys=True).encode()).hexdigest()[:12]
+    text = json.dumps([desc, library_digest(psdns.LIB_PATH)], sort_keys=True)
+    return hashlib.sha256(text.encode()).hexdigest()[:12]
 
 
 def cache_key(device: str, plan) -> str:
