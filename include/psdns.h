@@ -401,7 +401,11 @@ psdns_status psdns_spectra(psdns_plan* plan, const void* state, void* ws, double
 /* Per-kernel timing with HIP events on the launch stream (off by default).  Entries are the
  * step kernels by name, "aux" (initial field, conversions, spectra, pressure) and "step":
  * one whole RK4 step of psdns_step, around each graph replay or around the launches of an
- * eager step (its kernels are timed inside it).  median_ms and min_ms are over the
+ * eager step (its kernels are timed inside it).  An entry with no launches was not run as a
+ * kernel of its own: the forcing amplitude is computed inside the y inverse, or the pass per
+ * plane, except by the general kernels; where the y inverse, the x pass and the y forward run as
+ * one pass per plane (psdns_tune_passes) all three are timed as "x_pass"; "step_dt" is the step
+ * size, the step record and the stochastic forcings' update.  median_ms and min_ms are over the
  * launches since the previous psdns_get_timing. */
 typedef struct {
   char name[32];

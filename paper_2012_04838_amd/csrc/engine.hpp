@@ -92,8 +92,8 @@ namespace psdns {
 // Threads per column block: PSDNS_COL_MAXT, and at most 512 for FP32 columns longer than
 // 512 points.  There 512-thread blocks of 32 (128-byte tiles) or 16 (64-byte tiles) elements
 // per thread, with 256 registers each, beat 1024-thread blocks of 16 or 8 elements held in
-// 128 registers, spills included (1024^3: z inverse 6.1 against 7.1 ms, y inverse 9.0
-// against 9.7, y forward 3.8 against 4.2).
+// 128 registers, spills included (1024^3, 128-byte tiles: z inverse 5.4 against 7.1 ms, y
+// inverse 7.9 against 9.7, y forward 3.8 against 4.2).
 template <int N, typename T>
 constexpr int col_max_threads() {
   return (N > 512 && sizeof(T) == 4 && PSDNS_COL_MAXT > 512) ? 512 : PSDNS_COL_MAXT;
@@ -518,8 +518,7 @@ k_forcing_amplitude(const cpx<T>* __restrict__ sin, const SlotDev* __restrict__ 
 // exp(i pi ky / N).
 // With fsin (the stage input) the grid has one more row, the first: its first block of each
 // slot computes the forcing amplitude, which the z pass of the stage reads.  A small grid is
-// bound by its launches, and this one rides along (with the step size in the y forward, six
-// launches fewer of 22 per step; 32^3 FP64, together with fft.hpp's butterflies: 200 us a step to 180).
+// bound by its launches, about 4 us each, and this one of every stage rides along.
 // ---------------------------------------------------------------------------
 template <int N, typename T, int V, int DL = 0>
 __global__ void PSDNS_COL_BOUNDS(Cfg<N, T, V>::COL_THREADS)
@@ -806,7 +805,7 @@ k_x_pass(cpx<T>* __restrict__ bbuf, const cpx<T>* __restrict__ tw_g, const SlotD
   const int j = threadIdx.x % TT;
   // FP32 up to N = 512: the lane's factors live in registers for all nine transforms
   // of the line; FP64 and the lines of N = 1024 (18 factors a lane) keep them in LDS to leave
-  // registers for the line data.
+  // registers for the line data (1024^3 FP32: 12.4 ms, 15.9 with them in registers).
   constexpr bool kLong = E > 8;
   constexpr bool kRegTw = sizeof(T) == 4 && !kLong && N <= 512 && C::D.xreg;
   // FP32 short lines load every input up front; FP64 and 16-element lines load u3/omega1
@@ -1050,9 +1049,10 @@ k_x_pass(cpx<T>* __restrict__ bbuf, const cpx<T>* __restrict__ tw_g, const SlotD
 // registers, N E points of them per lane, and go back the same way.  A grid of this size is bound by
 // launches and by the chain of dependent steps inside a block, and a batch of them by the fields of B
 // (6 + 3S and 3 + S for S scalars) that the three passes write and read back.
-// (16 x 64^3 FP32, two scalars: 90 us against 151 in three passes; one 32^3 FP64 plane set, one
-// scalar: 14 us against 30.)  Larger planes do not fit: N^2 points are N^2 / 8 lanes of eight points, and each lane holds
-// eight values per point.
+// (16 x 64^3 FP32, two scalars: 107 us against 153 in three passes; one 32^3 FP64 plane set, one
+// scalar: 19 us against 30.)  Larger planes do not fit: N^2 points are N^2 / 8 lanes of eight
+// points, and each lane holds eight values per point.  16^3 would fit and gain (FP32, one scalar:
+// a step 80 us against 117), but the pass is neither compiled nor tested there; nor at 8^3.
 // A block reads every A field of its plane before it writes over it: outputs go to fields 0 .. 2
 // after the velocity's inputs, and a_s to 3 + s, which lies below the inputs 5 + 2s, 6 + 2s of every
 // scalar still to come.
@@ -2798,9 +2798,9 @@ void with_sched(int v, Fn&& fn) {
 
 // One right-hand-side evaluation and stage update, each pass with the schedule that
 // x.psched names for it.
-// schedule of the x pass of the phase-shift stage: three waves per SIMD with the stage
-// twiddles in LDS (its four half-spectrum entries per lane at N = 512 spill a little, and
-// it still ran 5% faster than schedule 0's two waves)
+// schedule of the x pass of the phase-shift stage: the stage factors in LDS, since in FP32 its half-
+// spectrum phases leave no registers for them (512^3, two scalars: 1.97 ms a launch, 2.42 in schedule
+// 0; FP64 holds none in either: 4.09)
 #ifndef PSDNS_PHASE_X
 #define PSDNS_PHASE_X 5
 #endif

@@ -25,8 +25,8 @@ namespace gen {
 constexpr int kMaxStages = 16;
 constexpr int kMaxOut = 3 * (6 + 3 * kMaxScalars);
 
-// Radices of the transform stages of an N-point line: eights, then one four or two for
-// the rest of the power of two, then the odd primes.
+// Radices of the transform stages of an N-point line of the statistics: eights, then one four
+// or two for the rest of the power of two, then the odd primes (step_factors: those of the step).
 struct Factors {
   int n, nst;
   int r[kMaxStages];
@@ -706,7 +706,7 @@ constexpr int x_waves() {
   return sizeof(T) == 4 ? (P <= 4 ? 4 : P <= 12 ? 3 : 2) : (P <= 10 ? 2 : 1);
 }
 
-// FULL: 64 lanes per line, known when compiled (520^3 FP32: 4.3 ms; with TL at run time 28 registers
+// FULL: 64 lanes per line, known when compiled (520^3 FP32: 4.4 ms; with TL at run time 28 registers
 // spill, 5.4)
 template <typename T, int P, bool FULL>
 __global__ void __launch_bounds__(kXThreads, (x_waves<T, P>()))
