@@ -547,28 +547,25 @@ psdns_status psdns_plan_create(const psdns_plan_params* p, psdns_plan** out) {
     delete plan;
     return hip_fail(e, "hipGetDevice");
   }
-  // root table (layout in common.hpp), computed in double precision: twiddles
-  // w_N^m = exp(-2 pi i m / N), the roots of the odd radices, the half-cell shift phases
+  // root table (layout in common.hpp): twiddles w_N^m = exp(-2 pi i m / N), the roots of the odd
+  // radices, the half-cell shift phases.  Angles and roots in extended precision, each rounded to
+  // FP64 once: the angle 2 pi m / N of an FP64 cosine carries a rounding of its own, which left the
+  // FP64 roots up to four units in the last place off.
   const int n = p->n;
   const size_t nent = (size_t)root_table_entries(n);
   const size_t twb = nent * plan->L.csize;
   std::vector<double> twd(2 * nent);
-  for (int m = 0; m < n; ++m) {
-    const double a = 2.0 * M_PI * (double)m / (double)n;
-    twd[2 * m] = std::cos(a);
-    twd[2 * m + 1] = -std::sin(a);
-  }
+  const long double pi = 3.14159265358979323846264338327950288L;
+  // entry i: exp(sgn i pi a / b)
+  auto root = [&](size_t i, int a, int b, double sgn) {
+    const long double t = pi * (long double)a / (long double)b;
+    twd[2 * i] = (double)std::cos(t);
+    twd[2 * i + 1] = sgn * (double)std::sin(t);
+  };
+  for (int m = 0; m < n; ++m) root(m, 2 * m, n, -1.0);
   for (int R : kOddRadices)
-    for (int m = 0; m < R; ++m) {
-      const size_t i = (size_t)n + kRootOff(R) + m;
-      twd[2 * i] = std::cos(2.0 * M_PI * m / R);
-      twd[2 * i + 1] = -std::sin(2.0 * M_PI * m / R);
-    }
-  for (int k = 0; k <= n / 2; ++k) {
-    const size_t i = (size_t)n + kShiftOff + k;
-    twd[2 * i] = std::cos(M_PI * k / n);
-    twd[2 * i + 1] = std::sin(M_PI * k / n);
-  }
+    for (int m = 0; m < R; ++m) root((size_t)n + kRootOff(R) + m, 2 * m, R, -1.0);
+  for (int k = 0; k <= n / 2; ++k) root((size_t)n + kShiftOff + k, k, n, 1.0);
   std::vector<char> host(twb);
   if (p->precision == 32) {
     float* f = reinterpret_cast<float*>(host.data());

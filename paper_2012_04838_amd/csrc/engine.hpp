@@ -183,11 +183,13 @@ constexpr int sched_count() {
   return kNumSched;
 }
 // Elements per thread of the column passes in the schedules that take the default: eight, and four
-// on lines of at most 32 points, whose blocks are so small that the length of a thread's chain
-// counts (32^3 FP64: fused z pass 20.2 us against 15.6, y inverse 11.5 against 9.6).
-template <int N>
-constexpr int default_elems(int e) {
-  return e > 0 ? e : (N <= 32 ? 4 : 8);
+// on lines of 16 points and, in FP64, of 32, whose blocks are so small that the length of a thread's
+// chain counts (32^3 FP64: fused z pass 20.2 us against 15.6, y inverse 11.5 against 9.6).  On 8
+// and 32 points four make a stage more (4 4 2 for 8 4), whose factors add 4 to 6% of rounding to an
+// FP32 right-hand side; in FP64 at 32 the correctly rounded roots make up for it.
+template <int N, typename T>
+constexpr int default_elems(int e = 0) {
+  return e > 0 ? e : (N == 16 || (N == 32 && sizeof(T) == 8) ? 4 : 8);
 }
 template <int N>
 constexpr int row_bytes(int b, int dflt) {
@@ -198,8 +200,8 @@ template <int N, typename T, int V = 0>
 struct Cfg {
   static constexpr Sched D = kSched[V];
   static constexpr bool F32 = sizeof(T) == 4;
-  using Col = ColCfg<N, T, default_elems<N>(F32 ? D.ec32 : D.ec64), row_bytes<N>(D.bytes, PSDNS_COL_BYTES)>;
-  using Fused = ColCfg<N, T, default_elems<N>(F32 ? D.ef32 : D.ef64), row_bytes<N>(F32 ? D.fb32 : D.fb64, F32 ? PSDNS_FB32 : PSDNS_FB64)>;
+  using Col = ColCfg<N, T, default_elems<N, T>(F32 ? D.ec32 : D.ec64), row_bytes<N>(D.bytes, PSDNS_COL_BYTES)>;
+  using Fused = ColCfg<N, T, default_elems<N, T>(F32 ? D.ef32 : D.ef64), row_bytes<N>(F32 ? D.fb32 : D.fb64, F32 ? PSDNS_FB32 : PSDNS_FB64)>;
   // columns per block and elements per thread of the column passes (z, y)
   static constexpr int W = Col::W;
   static constexpr int EC = Col::EC;
@@ -1064,7 +1066,7 @@ constexpr bool has_plane() {
 }
 template <int N, typename T>
 struct PlaneCfg {
-  static constexpr int E = N <= 32 ? 4 : 8;  // elements per thread, columns and lines
+  static constexpr int E = default_elems<N, T>();  // elements per thread, columns and lines
   static constexpr int TT = N / E;           // threads per column, lanes per line
   static constexpr int THREADS = N * TT;
   static constexpr int K = (N - 1) / 3, M = 2 * K + 1, KX = K + 1;
