@@ -6,6 +6,7 @@ Ops ops_general_f64();
 Ops ops_general(int precision) { return precision == 32 ? GEngine<float>::ops() : ops_general_f64(); }
 // (z, y) lines per block of the x pass
 int general_x_lines(int n, int precision, int batch) {
-  return gen::x_shape(gen::step_factors(n), precision == 32 ? 8 : 16, (long long)n * n * batch).lw;
+  const gen::Factors f = precision == 32 ? gen::step_factors<float>(n) : gen::step_factors<double>(n);
+  return gen::x_shape(f, precision == 32 ? 8 : 16, (long long)n * n * batch).lw;
 }
 }  // namespace psdns

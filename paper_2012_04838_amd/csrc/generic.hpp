@@ -25,8 +25,8 @@ namespace gen {
 constexpr int kMaxStages = 16;
 constexpr int kMaxOut = 3 * (6 + 3 * kMaxScalars);
 
-// Radices of the transform stages of an N-point line of the statistics: eights, then one four
-// or two for the rest of the power of two, then the odd primes (step_factors: those of the step).
+// Radices of the transform stages of an N-point line: eights, then one four or two for the rest of
+// the power of two, then the odd primes.
 struct Factors {
   int n, nst;
   int r[kMaxStages];
@@ -165,25 +165,30 @@ __device__ __forceinline__ cpx<T>* fft(cpx<T>* b0, cpx<T>* b1, const Factors& f,
 // from a functor (global memory) and their last one hands its outputs to one, so that a column
 // makes nst - 1 round trips through LDS with one barrier each, against nst + 1 with two more
 // barriers where every line is staged in and out (520^3 FP32, one scalar: y inverse 2.61
-// ms, 2.16 with this, the launch shapes and the addressing below).  Odd radices
-// come first: on a single line their stage writes R entries apart, free of bank conflicts for odd
-// R (radix 8 first: sixteen lanes on one bank), and the global loads of a wide first butterfly
-// are all in flight at once.  Power-of-two radices take the factors of fft.hpp's dft.
+// ms, 2.2 with this, the launch shapes and the addressing below).  Power-of-two radices take the
+// factors of fft.hpp's dft.
+//
+// With the odd radices first a line's stores are R entries apart, free of bank conflicts (radix 8
+// first: sixteen lanes on one bank), and the global loads of a wide first butterfly are all in
+// flight at once (520^3 FP32: 39.9 ms a step against 41.5; some small FP64 grids 20%).  FP64 takes
+// that order; its right-hand side rounds less than it did with roots from FP64 angles and the even
+// radices first (200^3: 1.1e-15 of it against 2.2e-15).  In FP32 the odd radices come last: first,
+// they add up to 15% of rounding (N = 104, 390, 520; 5% at 56), which nothing makes up for.
 // ---------------------------------------------------------------------------
+template <typename T>
 inline Factors step_factors(int N) {
   Factors f{};
   f.n = N;
   int m = N;
+  if (sizeof(T) == 4) {
+    f = factor(N);
+    m = 1;
+  }
   for (int p : {13, 11, 7, 5, 3})
     while (m % p == 0) {
       f.r[f.nst++] = p;
       m /= p;
     }
-  // at least two stages
-  if (m == N && m == 8) {
-    f.r[f.nst++] = 4;
-    m = 2;
-  }
   while (m % 8 == 0) {
     f.r[f.nst++] = 8;
     m /= 8;
@@ -193,6 +198,11 @@ inline Factors step_factors(int N) {
     m /= 4;
   }
   if (m % 2 == 0) f.r[f.nst++] = 2;
+  if (f.nst == 1) {  // at least two stages (N = 8)
+    f.nst = 2;
+    f.r[0] = 4;
+    f.r[1] = 2;
+  }
   return f;
 }
 

@@ -93,7 +93,7 @@ struct GEngine {
         g, gen::factor(g.N), sp, sh.W, sh.TT, shift);
   }
   static void x_pass(const Ctx& x, int shift, int umax, hipStream_t s) {
-    const Factors f = gen::step_factors(x.g.N);
+    const Factors f = gen::step_factors<T>(x.g.N);
     const gen::XShape sh = gen::x_shape(f, (int)sizeof(cpx<T>), (long long)x.g.N * x.g.N * x.g.batch);
     with_positions(sh.P, [&](auto p) { launch_x<decltype(p)::value>(x, sh, f, shift, umax, s); });
   }
@@ -104,7 +104,7 @@ struct GEngine {
   }
   static void z_inverse_step(const Ctx& x, const void* in, int shift, hipStream_t s) {
     const Geom& g = x.g;
-    const Factors f = gen::step_factors(g.N);
+    const Factors f = gen::step_factors<T>(g.N);
     const Shape sh = step_shape(f, g, g.M);
     const T scale = T(1) / (T(g.N) * T(g.N) * T(g.N));
     gen::k_z_inverse_step<T><<<dim3((g.KX + sh.W - 1) / sh.W, g.M, g.batch), sh.W * sh.TT, sh.lds, s>>>(
@@ -113,7 +113,7 @@ struct GEngine {
   }
   static void y_inverse_step(const Ctx& x, int shift, hipStream_t s) {
     const Geom& g = x.g;
-    const Factors f = gen::step_factors(g.N);
+    const Factors f = gen::step_factors<T>(g.N);
     const Shape sh = step_shape(f, g, g.N);
     gen::k_y_inverse_step<T><<<dim3((g.KX + sh.W - 1) / sh.W, g.N, g.batch), sh.W * sh.TT, sh.lds, s>>>(
         static_cast<const cpx<T>*>(x.abuf), static_cast<cpx<T>*>(x.bbuf), static_cast<const cpx<T>*>(x.tw), x.slots,
@@ -121,7 +121,7 @@ struct GEngine {
   }
   static void y_forward_step(const Ctx& x, void* out, int out_fields, int shift, hipStream_t s) {
     const Geom& g = x.g;
-    const Factors f = gen::step_factors(g.N);
+    const Factors f = gen::step_factors<T>(g.N);
     const Shape sh = step_shape(f, g, g.N);
     gen::k_y_forward_step<T><<<dim3((g.KX + sh.W - 1) / sh.W, g.N, g.batch), sh.W * sh.TT, sh.lds, s>>>(
         static_cast<const cpx<T>*>(x.bbuf), static_cast<cpx<T>*>(out), out_fields, static_cast<const cpx<T>*>(x.tw),
@@ -172,17 +172,17 @@ struct GEngine {
     sa.fband = x.fband;
     sa.stage = stage;
     TimedLaunch tl(x.timer, KID_ZFWD, s);
-    with_positions(gen::zf_positions(g.N, gen::zf_shape<T>(gen::step_factors(g.N), g).TT),
+    with_positions(gen::zf_positions(g.N, gen::zf_shape<T>(gen::step_factors<T>(g.N), g).TT),
                    [&](auto p) { launch_zf<decltype(p)::value>(x, sa, s); });
   }
   // z forward + update: P positions per thread of each column
   template <int P>
   static void launch_zf(const Ctx& x, const gen::GStage<T>& sa, hipStream_t s) {
     const Geom& g = x.g;
-    const Shape sh = gen::zf_shape<T>(gen::step_factors(g.N), g);
+    const Shape sh = gen::zf_shape<T>(gen::step_factors<T>(g.N), g);
     gen::k_z_forward_update<T, P><<<dim3((g.KX + sh.W - 1) / sh.W, g.M, g.batch), sh.W * sh.TT, sh.lds, s>>>(
         static_cast<const cpx<T>*>(x.abuf), g.sphere ? static_cast<const cpx<T>*>(x.akeep) : nullptr, sa,
-        static_cast<const cpx<T>*>(x.tw), x.slots, x.dyn, g, gen::step_factors(g.N), sh.W, sh.TT);
+        static_cast<const cpx<T>*>(x.tw), x.slots, x.dyn, g, gen::step_factors<T>(g.N), sh.W, sh.TT);
   }
 
   static void init_field(const Ctx& x, void* state, int slot, uint64_t seed, double kp, int kind, double energy,

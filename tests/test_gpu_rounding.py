@@ -57,6 +57,20 @@ def _fp32_error(N, dealias):
     return float(np.sqrt(np.mean(np.square(acc))))
 
 
+# mixed radix, 2/3 rule and phase shift (None: not measured)
+@pytest.mark.parametrize("N,cube,sphere", [(24, 2.154e-7, 2.202e-7), (40, 2.906e-7, 2.665e-7), (56, 2.391e-7, 2.372e-7),
+                                           (70, 2.695e-7, 2.448e-7), (98, 3.039e-7, 2.941e-7),
+                                           (104, 2.917e-7, 2.673e-7), (150, 3.628e-7, 3.389e-7),
+                                           (260, 4.549e-7, None), (520, 6.303e-7, None)])
+def test_fp32_rounding_of_the_general_kernels(N, cube, sphere):
+    for dealias, bar in ((psdns.DEALIAS_TWO_THIRDS, cube), (psdns.DEALIAS_PHASE_SPHERE, sphere)):
+        if bar is None:
+            continue
+        err = _fp32_error(N, dealias)
+        progress(f"[rounding] N={N} dealias={dealias} FP32 {err:.3e} (bar {bar:.3e})")
+        assert err < 1.02 * bar
+
+
 @pytest.mark.parametrize("N,cube,sphere", [(8, 8.732e-8, 1.138e-7), (16, 2.021e-7, 2.506e-7), (32, 2.537e-7, 2.704e-7),
                                            (64, 2.908e-7, 2.853e-7), (128, 3.555e-7, 3.415e-7),
                                            (256, 4.604e-7, 4.285e-7), (512, 6.550e-7, None)])
