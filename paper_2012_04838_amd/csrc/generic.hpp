@@ -716,7 +716,7 @@ constexpr int x_waves() {
   return sizeof(T) == 4 ? (P <= 4 ? 4 : P <= 12 ? 3 : 2) : (P <= 10 ? 2 : 1);
 }
 
-// FULL: 64 lanes per line, known when compiled (520^3 FP32: 4.4 ms; with TL at run time 28 registers
+// FULL: 64 lanes per line, known when compiled (520^3 FP32, odd radices first: 4.4 ms; with TL at run time 28 registers
 // spill, 5.4)
 template <typename T, int P, bool FULL>
 __global__ void __launch_bounds__(kXThreads, (x_waves<T, P>()))
