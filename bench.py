@@ -47,7 +47,7 @@ GRAD = ((0.0, 1.0, 0.0), (0.0, 1.0, 0.0))
 # reports null.
 _SAME = (0, 1, 2, 4, 5, 6)  # schedules with 128-byte kx tiles at this size (3 and 7: 64-byte)
 MEASURED_TRAFFIC = {
-    "src": "ba218cd936fe237b",
+    "src": "b83eecece6ebc7d0",
     "workload": (512, 2, 32),
     "bytes": {
         "z_inverse": {**{v: 2983.0e6 for v in _SAME}, 3: 3075.5e6, 7: 3065.9e6},
